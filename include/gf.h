@@ -107,11 +107,12 @@ typedef struct gf_params {
     long long start_sweep;  /* global index of the last sweep already done
                                (sets the reunitarisation phase on resume) */
     int storage;            /* GF_STORE_18 (default), GF_STORE_12 or GF_STORE_8 */
-    int lanes_per_site;     /* 0 = default (1; 2 for SU(4) and double SU(2)),
-                               else 1, 2, 4 or 8 lanes per site (SU(4): >= 2) */
+    int lanes_per_site;     /* 0 = default for the lattice size and storage
+                               form, else 1, 2, 4 or 8 lanes per site
+                               (SU(4): >= 2) */
     int block_threads;      /* 0 = default, else 64, 128, 192 or 256 */
     int nontemporal;        /* 1 = streaming (non-temporal) link loads/stores,
-                               0 = plain, -1 = default for the precision
+                               0 = plain, -1 = default for the lattice size
                                (SU(2)/SU(4) kernels always stream) */
     int use_graph;          /* 1 = replay each check period as a hipGraph */
     int timing;             /* 1 = time every half-sweep with hipEvents */
@@ -130,8 +131,8 @@ typedef struct gf_params {
                                flushed after every check. */
     int tile_order;         /* order in which a half-sweep's workgroups take
                                their tiles: 0 dispatch order, 1 XCD-contiguous
-                               shares; -1 = default (0). Results do not depend
-                               on it. */
+                               shares; -1 = default for the lattice size.
+                               Results do not depend on it. */
 } gf_params;
 
 /* Fill *p with the defaults for precision prec. */

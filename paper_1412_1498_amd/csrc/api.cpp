@@ -176,17 +176,75 @@ int check_omega(gf_ctx *ctx, double omega) {
     return GF_OK;
 }
 
-// Defaults from the schedule sweep at 48^4 on MI355X (blocked layout): one
-// lane per site with non-temporal link traffic; 128-thread workgroups, 256
-// for 12-real float storage. SU(4) links need LPS >= 2 (registers); the
-// SU(N) sweep at 48^4 is fastest with LPS 2 for SU(4) and for double SU(2).
-Schedule default_schedule(int prec, int nc, const gf_params &p) {
-    Schedule s;
-    s.lps = p.lanes_per_site > 0 ? p.lanes_per_site : ((nc == 4 || (nc == 2 && prec == GF_F64)) ? 2 : 1);
-    s.block = p.block_threads > 0 ? p.block_threads
-                                   : ((prec == GF_F32 && p.storage != GF_STORE_18) ? 256 : 128);
-    s.nt = p.nontemporal >= 0 ? p.nontemporal : 1;
-    s.order = p.tile_order >= 0 ? p.tile_order : 0;
+// Dynamic LDS that leaves room for three 128-thread workgroups on a CU
+// (160 KB): the occupancy limit of the sweep on fields beyond the
+// last-level cache.
+constexpr int SWEEP_LDS_3WG = 54272;
+
+// Occupancy limit for a schedule: six waves a CU for full and 12-real SU(3)
+// links in 128-thread workgroups once the fields are larger than the
+// last-level cache. More waves in flight only spread the accesses over more
+// DRAM pages and evict what the other half-sweep left in that cache: float
+// 18-real 48^4 563 -> 534 us, 12-real 354 -> 334 us, double 32^4 195 -> 191,
+// 48^4 1153 -> 1121 us. 8-real links, whose waves compute longer, lose by it
+// (float 48^4 261 -> 378 us).
+int sweep_lds(const Schedule &s, int nc, int nelem, double bytes) {
+    return nc == 3 && nelem != 4 && s.block == 128 && bytes > 230e6 ? SWEEP_LDS_3WG : 0;
+}
+
+// Default schedule by lattice size (`sites` and `bytes` of all members), from
+// sweeps over every lane count, workgroup size, access kind and tile order on
+// lattices from 4^4 to 48^4 in all six forms of SU(3) links; the lines below
+// are within 2 % of the best schedule in the geometric mean.
+Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, double bytes, const gf_params &p) {
+    Schedule s{};
+    const bool f64 = prec == GF_F64, c8 = nc == 3 && nelem == 4;
+    const double half = 0.5 * sites;
+    if (nc != 3) {
+        // SU(4) links need two lanes a site (registers); double SU(2) is fastest with two
+        s.lps = (nc == 4 || f64) ? 2 : 1;
+        s.block = 128;
+        s.nt = 1;
+        s.order = 0;
+    } else if (bytes <= 230e6) {
+        // Fields in the last-level cache. Few sites: more lanes a site shorten
+        // a wave's work while the chip has idle SIMDs anyway (1024 of them);
+        // 8-real lanes have the coding of their links to share as well. 8^4
+        // in double 7.4 us with one lane, 5.5 us with four; 8-real 10.7 us with
+        // one, 5.6 us with eight. From there two lanes, whose waves fit
+        // two or three to a SIMD (double 20^4 32.9 -> 29.2 us), except float
+        // 12-real links beyond 1e5 sites, where one lane fits twice as well.
+        // Tiles in contiguous XCD shares: neighbouring tiles share the cache
+        // lines at their seams (22x18x26x30 float 31.5 -> 29.0 us).
+        if (c8) s.lps = half * 8 <= 512 * 64 ? 8 : half * 4 <= 1024 * 64 ? 4 : 2;
+        else s.lps = half * 4 <= 512 * 64 ? 4 : 2;
+        s.block = half * s.lps <= 4096 * 64 ? 64 : 128;
+        if (!f64 && nelem == 6 && half > 60000) { s.lps = 1; s.block = 256; }
+        // streaming access only just above the L2s (32 MB), which plain access
+        // keeps filled with lines that are evicted before their next use:
+        // double 16^4 13.7 us plain, 11.6 us streaming
+        s.nt = bytes > 16e6 && bytes < 48e6;
+        s.order = n == 1;  // an ensemble's members converge one by one and would empty their XCD's share
+    } else if (c8) {
+        s.lps = f64 ? 2 : 1;
+        s.block = f64 ? 64 : 128;
+        s.nt = 0;
+        s.order = 0;
+    } else {
+        // plain access keeps the end of one half-sweep in the last-level cache
+        // for the start of the next; of 3 GB (double 48^4) that is too little
+        // to pay (1121 us streaming, 1128 us plain)
+        const bool huge = bytes > 2.2e9;
+        s.lps = f64 || huge ? 2 : 1;
+        s.block = 128;
+        s.nt = huge;
+        s.order = huge && n == 1;
+    }
+    if (p.lanes_per_site > 0) s.lps = p.lanes_per_site;
+    if (p.block_threads > 0) s.block = p.block_threads;
+    if (p.nontemporal >= 0) s.nt = p.nontemporal;
+    if (p.tile_order >= 0) s.order = p.tile_order;
+    s.lds = sweep_lds(s, nc, nelem, bytes);
     return s;
 }
 
@@ -346,14 +404,21 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
     if (p.reunit_every < 0) return GF_EINVAL;
     if (p.storage != GF_STORE_18 && p.storage != GF_STORE_12 && p.storage != GF_STORE_8) return GF_EINVAL;
     if (nc != 3 && p.storage != GF_STORE_18) return GF_EUNSUPPORTED;  // 12-/8-real are SU(3) only
-    Schedule s = default_schedule(prec, nc, p);
+    const int nelem = nc != 3 ? nc * nc : (p.storage == GF_STORE_12 ? 6 : p.storage == GF_STORE_8 ? 4 : 9);
+    double sites = 0.0, bytes = 0.0;
+    for (int c = 0; c < n; c++) {
+        const Geom g = make_geom(dims + 4 * c, nelem);
+        sites += g.V;
+        bytes += (double)field_complex(g) * (prec == GF_F64 ? 16 : 8);
+    }
+    Schedule s = default_schedule(prec, nc, nelem, n, sites, bytes, p);
     if (check_schedule(&tmp, s, nc) != GF_OK) return GF_EINVAL;
 
     gf_ctx *ctx = new gf_ctx();
     ctx->n = n;
     ctx->prec = prec;
     ctx->nc = nc;
-    ctx->nelem = nc != 3 ? nc * nc : (p.storage == GF_STORE_12 ? 6 : p.storage == GF_STORE_8 ? 4 : 9);
+    ctx->nelem = nelem;
     ctx->stream = (hipStream_t)stream;
     ctx->p = p;
     ctx->sched = s;
@@ -775,6 +840,11 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
         key << "|" << g.nx << "x" << g.ny << "x" << g.nz << "x" << g.nt << "g" << ctx->desc[c].gauge;
     }
     const std::string k = key.str();
+    auto total_bytes = [&]() {
+        double b = 0.0;
+        for (int c = 0; c < ctx->n; c++) b += (double)gf_field_bytes(ctx, c);
+        return b;
+    };
     if (cache_path) {
         std::ifstream in(cache_path);
         std::string line, found;
@@ -784,6 +854,7 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
             Schedule s{};
             std::istringstream is(found);
             if (is >> s.lps >> s.block >> s.nt >> s.order && check_schedule(ctx, s, ctx->nc) == GF_OK) {
+                s.lds = sweep_lds(s, ctx->nc, ctx->nelem, total_bytes());
                 ctx->sched = s;
                 return build_tiles(ctx);
             }
@@ -830,7 +901,8 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
                 // others still carry the large members' tiles (measured on the uneven
                 // ensemble: tuned with every member active it won, then ran 11 % slower)
                 for (int order = 0; order < (ctx->n == 1 ? 2 : 1) && rc == GF_OK; order++) {
-                    Schedule s{lps_list[li], block_list[bi], nt, order};
+                    Schedule s{lps_list[li], block_list[bi], nt, order, 0};
+                    s.lds = sweep_lds(s, ctx->nc, ctx->nelem, total_bytes());
                     if (ctx->nc == 4 && s.lps < 2) continue;       // registers
                     if (ctx->nc != 3 && nt != 1) continue;         // SU(N) links are always non-temporal
                     ctx->sched = s;
@@ -1088,7 +1160,7 @@ void gf_host_su2_step(const double b[4], double omega, double r[4]) {
 
 void gf_host_trig(double x, double y, double out[3]) {
     if (!out) return;
-    gf_sincos(x, &out[0], &out[1]);
+    gf_sincos(gf_trig(), x, &out[0], &out[1]);
     out[2] = gf_atan2(y, x);
 }
 

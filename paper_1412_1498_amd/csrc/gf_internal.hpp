@@ -138,6 +138,7 @@ struct Schedule {
     int block;      // threads per workgroup
     int nt;         // non-temporal loads/stores
     int order;      // sweep tiles: 0 in dispatch order, 1 XCD-contiguous (xcd_tile)
+    int lds;        // dynamic LDS per workgroup: unused by the kernel, it limits the workgroups on a CU
 };
 
 // ---- launchers (defined in the .hip files) ----

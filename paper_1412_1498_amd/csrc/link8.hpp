@@ -44,6 +44,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "gf_math.hpp"
+
 namespace gf {
 
 #define GF_HD __host__ __device__ __forceinline__
@@ -51,24 +53,38 @@ namespace gf {
 // Reciprocal and square root. In float on the GPU these are the hardware
 // instructions (about 1 ulp) rather than the correctly rounded sequences:
 // the format's own rounding (a few ulp) dominates, and the exact sequences
-// made the float 8-real sweep instruction-bound. Double and host code use
-// the correctly rounded operations.
+// made the float 8-real sweep instruction-bound. In double they are gf_rcp
+// and gf_sqrt, which round like the general operations but skip their range
+// scaling: a site's 8 links take 40 reciprocals and 32 square roots, half of
+// the double sweep's instructions in their general form. Float host code
+// uses the general operations.
 template <typename R> GF_HD R link8_rcp(R x) {
+    if constexpr (sizeof(R) == 8) return gf_rcp(x);
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (sizeof(R) == 4) return __builtin_amdgcn_rcpf(x);
 #endif
     return R(1) / x;
 }
 template <typename R> GF_HD R link8_sqrt(R x) {
+    if constexpr (sizeof(R) == 8) return gf_sqrt(x);
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (sizeof(R) == 4) return __builtin_amdgcn_sqrtf(x);
 #endif
     return sqrt(x);
 }
 
+// a b + c d: one multiply and one FMA in double; in float both products are
+// rounded first (a fused form is as exact, but fields stored with it drift
+// from fields stored without it, by up to 1e-3 at the links with tiny |U00|).
+template <typename R>
+GF_HD R link8_dot(R a, R b, R c, R d) {
+    if constexpr (sizeof(R) == 8) return fma(a, b, c * d);
+    else return a * b + c * d;
+}
+
 template <typename R>
 GF_HD R link8_phase_code(R re, R im) {
-    const R m = link8_sqrt<R>(re * re + im * im);
+    const R m = link8_sqrt<R>(link8_dot<R>(re, re, im, im));
     if (!(m > R(0))) return R(4);  // z = 0: a code outside [-2, 2] that decodes to 0
     const R t = im * link8_rcp<R>(m + fabs(re));
     return re >= R(0) ? t : (t >= R(0) ? R(2) - t : R(-2) - t);
@@ -80,8 +96,8 @@ GF_HD void link8_phase_decode(R p, R *c, R *s) {
     const bool zero = fabs(p) > R(3);
     const bool neg = fabs(p) > R(1);
     const R t = neg ? copysign(R(2) - fabs(p), p) : p;
-    const R d = link8_rcp<R>(R(1) + t * t);
-    const R ac = (R(1) - t * t) * d;
+    const R d = link8_rcp<R>(link8_dot<R>(t, t, R(1), R(1)));
+    const R ac = link8_dot<R>(-t, t, R(1), R(1)) * d;
     *s = zero ? R(0) : R(2) * t * d;
     *c = zero ? R(0) : (neg ? -ac : ac);
 }
@@ -103,9 +119,9 @@ GF_HD void link8_compress(const R *re, const R *im, R *sre, R *sim) {
 template <typename R>
 GF_HD void link8_reconstruct(const R *sre, const R *sim, R *re, R *im) {
     const R a2r = sre[0], a2i = sim[0], a3r = sre[1], a3i = sim[1];
-    const R n2 = a2r * a2r + a2i * a2i + (a3r * a3r + a3i * a3i);
+    const R n2 = link8_dot<R>(a2r, a2r, a2i, a2i) + link8_dot<R>(a3r, a3r, a3i, a3i);
     const bool deg = !(n2 > R(0));        // U01 = U02 = 0: the slot holds U11
-    const R sl = sre[2] * sre[2] + sim[2] * sim[2];
+    const R sl = link8_dot<R>(sre[2], sre[2], sim[2], sim[2]);
     const R b1r = deg ? R(0) : sre[2], b1i = deg ? R(0) : sim[2];
     R s, c;
     link8_phase_decode<R>(sre[3], &c, &s);
@@ -113,31 +129,26 @@ GF_HD void link8_reconstruct(const R *sre, const R *sim, R *re, R *im) {
     const R a1r = m1 * c, a1i = m1 * s;
     link8_phase_decode<R>(sim[3], &c, &s);
     // |U20| in general; |U12| = sqrt(1 - |U11|^2) in the n2 = 0 case
-    const R m3 = link8_sqrt<R>(fmax(deg ? R(1) - sl : n2 - sl, R(0)));
+    const R m3 = link8_sqrt<R>(fmax((deg ? R(1) : n2) - sl, R(0)));
     const R zr = m3 * c, zi = m3 * s;
     const R c1r = deg ? R(0) : zr, c1i = deg ? R(0) : zi;
     // conj(a1) a2 b1, conj(a1) a3 b1
-    const R pr = a1r * a2r + a1i * a2i, pi = a1r * a2i - a1i * a2r;   // conj(a1) a2
-    const R qr = a1r * a3r + a1i * a3i, qi = a1r * a3i - a1i * a3r;   // conj(a1) a3
-    const R t1r = pr * b1r - pi * b1i, t1i = pr * b1i + pi * b1r;
-    const R t2r = qr * b1r - qi * b1i, t2i = qr * b1i + qi * b1r;
+    const R pr = link8_dot<R>(a1r, a2r, a1i, a2i), pi = link8_dot<R>(a1r, a2i, -a1i, a2r);   // conj(a1) a2
+    const R qr = link8_dot<R>(a1r, a3r, a1i, a3i), qi = link8_dot<R>(a1r, a3i, -a1i, a3r);   // conj(a1) a3
+    const R t1r = link8_dot<R>(pr, b1r, -pi, b1i), t1i = link8_dot<R>(pr, b1i, pi, b1r);
+    const R t2r = link8_dot<R>(qr, b1r, -qi, b1i), t2i = link8_dot<R>(qr, b1i, qi, b1r);
     // conj(a3) conj(c1) = conj(a3 c1), conj(a2) conj(c1) = conj(a2 c1)
-    const R u3r = a3r * c1r - a3i * c1i, u3i = -(a3r * c1i + a3i * c1r);
-    const R u2r = a2r * c1r - a2i * c1i, u2i = -(a2r * c1i + a2i * c1r);
-    R b2r, b2i, b3r, b3i;
-    if (n2 > R(0)) {
-        const R inv = link8_rcp<R>(n2);
-        b2r = -(t1r + u3r) * inv; b2i = -(t1i + u3i) * inv;
-        b3r = (u2r - t2r) * inv;  b3i = (u2i - t2i) * inv;
-    } else {  // U01 = U02 = 0: U11 from the slot, U12 from its phase code and modulus
-        b2r = sre[2]; b2i = sim[2];
-        b3r = zr; b3i = zi;
-    }
+    const R u3r = link8_dot<R>(a3r, c1r, -a3i, c1i), u3i = -link8_dot<R>(a3r, c1i, a3i, c1r);
+    const R u2r = link8_dot<R>(a2r, c1r, -a2i, c1i), u2i = -link8_dot<R>(a2r, c1i, a2i, c1r);
+    const R inv = link8_rcp<R>(deg ? R(1) : n2);
+    // n2 = 0: U11 from the slot, U12 from its phase code and modulus
+    const R b2r = deg ? sre[2] : -(t1r + u3r) * inv, b2i = deg ? sim[2] : -(t1i + u3i) * inv;
+    const R b3r = deg ? zr : (u2r - t2r) * inv, b3i = deg ? zi : (u2i - t2i) * inv;
     // c2 = -conj(a1 b3 - a3 b1), c3 = conj(a1 b2 - a2 b1)
-    const R x2r = a1r * b3r - a1i * b3i - (a3r * b1r - a3i * b1i);
-    const R x2i = a1r * b3i + a1i * b3r - (a3r * b1i + a3i * b1r);
-    const R x3r = a1r * b2r - a1i * b2i - (a2r * b1r - a2i * b1i);
-    const R x3i = a1r * b2i + a1i * b2r - (a2r * b1i + a2i * b1r);
+    const R x2r = link8_dot<R>(a1r, b3r, -a1i, b3i) - link8_dot<R>(a3r, b1r, -a3i, b1i);
+    const R x2i = link8_dot<R>(a1r, b3i, a1i, b3r) - link8_dot<R>(a3r, b1i, a3i, b1r);
+    const R x3r = link8_dot<R>(a1r, b2r, -a1i, b2i) - link8_dot<R>(a2r, b1r, -a2i, b1i);
+    const R x3i = link8_dot<R>(a1r, b2i, a1i, b2r) - link8_dot<R>(a2r, b1i, a2i, b1r);
     re[0] = a1r; im[0] = a1i;
     re[1] = a2r; im[1] = a2i;
     re[2] = a3r; im[2] = a3i;

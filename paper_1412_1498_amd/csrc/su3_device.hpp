@@ -63,31 +63,32 @@ __device__ __forceinline__ void rebuild_row2(Mat<R> &m) {
     }
 }
 
+// A link from its NE stored complex values. NE = 9: full matrix; NE = 6:
+// rows 0, 1; NE = 4: the 8-real form of link8.hpp.
+template <typename R, int NE>
+__device__ __forceinline__ void unpack_link(const typename V2<R>::type v[NE], Mat<R> &m) {
+    if constexpr (NE == 4) {
+        R sre[4], sim[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) { sre[e] = v[e].x; sim[e] = v[e].y; }
+        link8_reconstruct<R>(sre, sim, m.re, m.im);
+    } else {
+#pragma unroll
+        for (int e = 0; e < NE; e++) { m.re[e] = v[e].x; m.im[e] = v[e].y; }
+        if constexpr (NE == 6) rebuild_row2(m);
+    }
+}
+
 // Link whose element 0 sits at complex offset `off` (see link_off); element
-// e is BLK complex values further. NE = 9: full matrix; NE = 6: rows 0, 1;
-// NE = 4: the 8-real form of link8.hpp.
+// e is BLK complex values further.
 template <typename R, int NE, bool NT>
 __device__ __forceinline__ void load_link(Mat<R> &m, const gchar *base, long long off) {
     typedef typename V2<R>::type v2;
     const gchar *p = base + off * (long long)sizeof(v2);
-    if constexpr (NE == 4) {
-        R sre[4], sim[4];
+    v2 v[NE];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            v2 v = ld<NT, v2>(p, (uint32_t)(e * BLK * sizeof(v2)));
-            sre[e] = v.x;
-            sim[e] = v.y;
-        }
-        link8_reconstruct<R>(sre, sim, m.re, m.im);
-    } else {
-#pragma unroll
-        for (int e = 0; e < NE; e++) {
-            v2 v = ld<NT, v2>(p, (uint32_t)(e * BLK * sizeof(v2)));
-            m.re[e] = v.x;
-            m.im[e] = v.y;
-        }
-        if constexpr (NE == 6) rebuild_row2(m);
-    }
+    for (int e = 0; e < NE; e++) v[e] = ld<NT, v2>(p, (uint32_t)(e * BLK * sizeof(v2)));
+    unpack_link<R, NE>(v, m);
 }
 
 template <typename R, int NE, bool NT>
@@ -167,6 +168,23 @@ __device__ __forceinline__ void rotate_rows(Mat<R> &m, int a, int b, const R g[4
     }
 }
 
+// r / |r| for a row of three complex numbers. Rows of float links take one
+// reciprocal square root and six products (the result is rounded to float);
+// double links keep the correctly rounded quotients.
+template <typename R>
+__device__ __forceinline__ void normalise_row(double r[3], double i[3]) {
+    const double n2 = r[0] * r[0] + i[0] * i[0] + r[1] * r[1] + i[1] * i[1] + r[2] * r[2] + i[2] * i[2];
+    if constexpr (sizeof(R) == 4) {
+        const double f = gf_rsqrt(n2);
+#pragma unroll
+        for (int c = 0; c < 3; c++) { r[c] *= f; i[c] *= f; }
+    } else {
+        const double n = sqrt(n2);
+#pragma unroll
+        for (int c = 0; c < 3; c++) { r[c] /= n; i[c] /= n; }
+    }
+}
+
 // Gram-Schmidt reunitarisation in double: r0 /= |r0|; r1 -= (r0^+ r1) r0;
 // r1 /= |r1|; r2 = conj(r0 x r1). Result rounded to the link precision.
 template <typename R>
@@ -177,10 +195,7 @@ __device__ __forceinline__ void reunitarise(Mat<R> &m) {
         r0r[c] = m.re[c]; r0i[c] = m.im[c];
         r1r[c] = m.re[3 + c]; r1i[c] = m.im[3 + c];
     }
-    double n0 = sqrt(r0r[0] * r0r[0] + r0i[0] * r0i[0] + r0r[1] * r0r[1] + r0i[1] * r0i[1] +
-                     r0r[2] * r0r[2] + r0i[2] * r0i[2]);
-#pragma unroll
-    for (int c = 0; c < 3; c++) { r0r[c] /= n0; r0i[c] /= n0; }
+    normalise_row<R>(r0r, r0i);
     double pr = 0.0, pi = 0.0;  // r0^+ r1
 #pragma unroll
     for (int c = 0; c < 3; c++) {
@@ -192,10 +207,7 @@ __device__ __forceinline__ void reunitarise(Mat<R> &m) {
         r1r[c] -= pr * r0r[c] - pi * r0i[c];
         r1i[c] -= pr * r0i[c] + pi * r0r[c];
     }
-    double n1 = sqrt(r1r[0] * r1r[0] + r1i[0] * r1i[0] + r1r[1] * r1r[1] + r1i[1] * r1i[1] +
-                     r1r[2] * r1r[2] + r1i[2] * r1i[2]);
-#pragma unroll
-    for (int c = 0; c < 3; c++) { r1r[c] /= n1; r1i[c] /= n1; }
+    normalise_row<R>(r1r, r1i);
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;

@@ -24,9 +24,7 @@ namespace {
 
 struct Q4n { double v[4]; };
 
-// Out of line, as in the SU(3) kernel, so the solve's double temporaries do
-// not compete with the link registers.
-__device__ __attribute__((noinline)) Q4n sun_su2_step(Q4n b, double omega) {
+__device__ __forceinline__ Q4n sun_su2_step(Q4n b, double omega) {
     Q4n r;
     gf_su2_overrelax(b.v, omega, r.v);
     return r;
@@ -41,10 +39,10 @@ __device__ __forceinline__ void rot_rows_n(DMN<N> &m, int a, int b, const Q4n &g
     for (int c = 0; c < N; c++) {
         const double xr = m.re[N * a + c], xi = m.im[N * a + c];
         const double yr = m.re[N * b + c], yi = m.im[N * b + c];
-        m.re[N * a + c] = ar * xr - ai * xi + (br * yr - bi * yi);
-        m.im[N * a + c] = ar * xi + ai * xr + (br * yi + bi * yr);
-        m.re[N * b + c] = -br * xr - bi * xi + (ar * yr + ai * yi);
-        m.im[N * b + c] = -br * xi + bi * xr + (ar * yi - ai * yr);
+        m.re[N * a + c] = fma(ar, xr, fma(-ai, xi, fma(br, yr, -bi * yi)));
+        m.im[N * a + c] = fma(ar, xi, fma(ai, xr, fma(br, yi, bi * yr)));
+        m.re[N * b + c] = fma(-br, xr, fma(-bi, xi, fma(ar, yr, ai * yi)));
+        m.im[N * b + c] = fma(-br, xi, fma(bi, xr, fma(ar, yi, -ai * yr)));
     }
 }
 

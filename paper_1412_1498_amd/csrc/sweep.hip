@@ -16,6 +16,17 @@
 // is that of rotating the links after every subgroup, with two fewer
 // roundings of each link.
 //
+// What bounds it: memory, for every form but the smallest lattices. The rate
+// depends on how many waves are in flight (too few: memory idles while they
+// solve; too many on a field beyond the caches: they evict each other's
+// neighbours), hence the lane count, workgroup size and occupancy limit by
+// lattice size in default_schedule (api.cpp). Half-sweeps at 48^4, before and
+// after the solve was shortened, its registers trimmed and the tiles taken
+// from alternating ends: float 18-real 546-552 -> 530-534 us, 12-real 373 ->
+// 334, 8-real 372 -> 260, double 18-real 1146 -> 1121, 8-real 684 -> 487;
+// at 22x18x26x30 42.2 -> 29.3, 27.0 -> 21.8, 31.6 -> 21.4, 79.1 -> 53.7,
+// 52.8 -> 30.6.
+//
 // Schedules: LPS lanes cooperate on a site (LPS = 1, 2, 4, 8), each holding
 // 8/LPS links. Link slots are ordered (fwd 0, bwd 0, fwd 1, bwd 1, ...,
 // fwd 3, bwd 3); a lane owns consecutive slots and K is summed over slots in
@@ -32,31 +43,40 @@ struct DM {
     double re[9], im[9];
 };
 
-// The SU(2) solve with over-relaxation, kept out of line: inlined, its
-// double-precision temporaries are scheduled across the link registers and
-// raise the kernel's VGPR count by about half. Arguments and result travel
-// in registers.
-struct Q4 { double v[4]; };
+// A complex double, and products of one FMA chain per component:
+// a x + b y, -conj(b) x + conj(a) y (the two rows of an SU(2) rotation),
+// a x, conj(a) x.
+struct Cz {
+    double re, im;
+};
 
-__device__ __attribute__((noinline)) Q4 su2_step(Q4 b, double omega) {
-    Q4 r;
-    gf_su2_overrelax(b.v, omega, r.v);
-    return r;
+__device__ __forceinline__ Cz rot_top(Cz a, Cz b, Cz x, Cz y) {
+    return Cz{fma(a.re, x.re, fma(-a.im, x.im, fma(b.re, y.re, -b.im * y.im))),
+              fma(a.re, x.im, fma(a.im, x.re, fma(b.re, y.im, b.im * y.re)))};
 }
 
-// Rows a, b of m <- g (rows a, b of m); g = [[g0 + i g3, g2 + i g1],
-// [-g2 + i g1, g0 - i g3]] in double.
-__device__ __forceinline__ void rot_rows_d(DM &m, int a, int b, const Q4 &g) {
-    const double ar = g.v[0], ai = g.v[3], br = g.v[2], bi = g.v[1];
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        const double xr = m.re[3 * a + c], xi = m.im[3 * a + c];
-        const double yr = m.re[3 * b + c], yi = m.im[3 * b + c];
-        m.re[3 * a + c] = ar * xr - ai * xi + (br * yr - bi * yi);
-        m.im[3 * a + c] = ar * xi + ai * xr + (br * yi + bi * yr);
-        m.re[3 * b + c] = -br * xr - bi * xi + (ar * yr + ai * yi);
-        m.im[3 * b + c] = -br * xi + bi * xr + (ar * yi - ai * yr);
-    }
+__device__ __forceinline__ Cz rot_bottom(Cz a, Cz b, Cz x, Cz y) {
+    return Cz{fma(-b.re, x.re, fma(-b.im, x.im, fma(a.re, y.re, a.im * y.im))),
+              fma(-b.re, x.im, fma(b.im, x.re, fma(a.re, y.im, -a.im * y.re)))};
+}
+
+__device__ __forceinline__ Cz cz_mul(Cz a, Cz x) {
+    return Cz{fma(a.re, x.re, -a.im * x.im), fma(a.re, x.im, a.im * x.re)};
+}
+
+__device__ __forceinline__ Cz cz_mul_conj(Cz a, Cz x) {
+    return Cz{fma(a.re, x.re, a.im * x.im), fma(a.re, x.im, -a.im * x.re)};
+}
+
+// First row (al, be) of the SU(2) element g^omega of eq. (6) for the 2x2
+// block [[aa, ab], [ba, bb]] of K; the second row is (-conj be, conj al).
+__device__ __forceinline__ void subgroup_step(Cz aa, Cz ab, Cz ba, Cz bb, double omega, Cz &al, Cz &be) {
+    const double q[4] = {0.5 * (aa.re + bb.re), 0.5 * (ab.im + ba.im), 0.5 * (ab.re - ba.re),
+                         0.5 * (aa.im - bb.im)};
+    double r[4];
+    gf_su2_overrelax(q, omega, r);
+    al = Cz{r[0], r[3]};
+    be = Cz{r[2], r[1]};
 }
 
 // o = g u (forward link) or o = u g^dagger (backward link), g in the link
@@ -112,24 +132,37 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
     constexpr int L = 8 / LPS;  // links per lane
     const Geom &g = d.g;
     gchar *U = as_global(d.U);
-    const SiteNbr nb = site_neighbours(g, p, h);
+    SiteNbr nb = site_neighbours(g, p, h);
     const bool landau = d.gauge == 0;
 
-    long long off[L];
     bool bwd[L], in[L];
 #pragma unroll
     for (int k = 0; k < L; k++) {
         const int slot = sub * L + k;
-        const int mu = slot >> 1;
-        const bool b = (slot & 1) != 0;  // compile-time unless LPS == 8
-        off[k] = b ? link_off(g, mu, 1 - p, pick4(nb.hb, mu)) : link_off(g, mu, p, h);
-        bwd[k] = b;
-        in[k] = landau || mu != 3;
+        bwd[k] = (slot & 1) != 0;  // compile-time unless LPS == 8
+        in[k] = landau || (slot >> 1) != 3;
     }
+    auto slot_off = [&](int k) {
+        const int mu = (sub * L + k) >> 1;
+        return bwd[k] ? link_off(g, mu, 1 - p, pick4(nb.hb, mu)) : link_off(g, mu, p, h);
+    };
 
+    typedef typename V2<R>::type v2;
+    const gchar *base[L];
+    v2 raw[L][NE];
     Mat<R> w[L];
 #pragma unroll
-    for (int k = 0; k < L; k++) load_link<R, NE, NT>(w[k], U, off[k]);
+    for (int k = 0; k < L; k++) base[k] = U + slot_off(k) * (long long)sizeof(v2);
+#pragma unroll
+    for (int k = 0; k < L; k++)
+#pragma unroll
+        for (int e = 0; e < NE; e++) raw[k][e] = ld<NT, v2>(base[k], (uint32_t)(e * BLK * sizeof(v2)));
+    // every load is issued before the first value is used: left to itself the
+    // scheduler defers loads into the solves to save registers, and a wave
+    // then waits for several memory latencies instead of one
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < L; k++) unpack_link<R, NE>(raw[k], w[k]);
 
     // K = sum over slots of U (forward) or U^dagger (backward), promoted to
     // double; per element, the lane's slots are summed in place in the fixed
@@ -165,32 +198,46 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
         }
     }
 
-    // three subgroup steps on K: (0,1), (0,2), (1,2)
-    Q4 gs[3];
-#pragma unroll
-    for (int sg = 0; sg < 3; sg++) {
-        const int a = sg == 2 ? 1 : 0, b = sg == 0 ? 1 : 2;
-        const int aa = 4 * a, bb = 4 * b, ab = 3 * a + b, ba = 3 * b + a;
-        Q4 q;
-        q.v[0] = 0.5 * (K.re[aa] + K.re[bb]);
-        q.v[1] = 0.5 * (K.im[ab] + K.im[ba]);
-        q.v[2] = 0.5 * (K.re[ab] - K.re[ba]);
-        q.v[3] = 0.5 * (K.im[aa] - K.im[bb]);
-        gs[sg] = su2_step(q, d.omega);
-        if (sg < 2) rot_rows_d(K, a, b, gs[sg]);
-    }
+    // Three subgroup steps on K: (0,1), (0,2), (1,2). Only the entries of the
+    // rotated K that a later step reads are formed: K01 and K02 of the rotated
+    // row 0, K11 and K12 of row 1, then K21 and K22 of row 2.
+    auto k_at = [&](int e) { return Cz{K.re[e], K.im[e]}; };
+    Cz a1, b1, a2, b2, a3, b3;
+    subgroup_step(k_at(0), k_at(1), k_at(3), k_at(4), d.omega, a1, b1);
+    const Cz k00 = rot_top(a1, b1, k_at(0), k_at(3)), k01 = rot_top(a1, b1, k_at(1), k_at(4)),
+             k02 = rot_top(a1, b1, k_at(2), k_at(5));
+    const Cz k11 = rot_bottom(a1, b1, k_at(1), k_at(4)), k12 = rot_bottom(a1, b1, k_at(2), k_at(5));
+    subgroup_step(k00, k02, k_at(6), k_at(8), d.omega, a2, b2);
+    subgroup_step(k11, k12, rot_bottom(a2, b2, k01, k_at(7)), rot_bottom(a2, b2, k02, k_at(8)), d.omega, a3, b3);
 
-    // G = G3 G2 G1 (double), rounded to the link precision
-    DM T;
-#pragma unroll
-    for (int e = 0; e < 9; e++) { T.re[e] = (e % 4 == 0) ? 1.0 : 0.0; T.im[e] = 0.0; }
-    rot_rows_d(T, 0, 1, gs[0]);
-    rot_rows_d(T, 0, 2, gs[1]);
-    rot_rows_d(T, 1, 2, gs[2]);
+    // G = G3 G2 G1 (double), rounded to the link precision. With every G a 2x2
+    // block and a 1, the rows are
+    //   row 0:  (a2 a1, a2 b1, b2)
+    //   rows 1, 2: G3 on (-conj b1, conj a1, 0) and
+    //              (-conj(b2) a1, -conj(b2) b1, conj a2).
+    // (Three general row rotations of the identity took 150 more of the
+    // wave's 2300 vector instructions, most of them on zeros.)
     Mat<R> G;
-#pragma unroll
-    for (int e = 0; e < 9; e++) { G.re[e] = (R)T.re[e]; G.im[e] = (R)T.im[e]; }
+    auto set = [&](int e, Cz z) { G.re[e] = (R)z.re; G.im[e] = (R)z.im; };
+    const Cz mb2 = Cz{-b2.re, -b2.im};
+    const Cz t10 = Cz{-b1.re, b1.im}, t11 = Cz{a1.re, -a1.im};
+    const Cz t20 = cz_mul_conj(mb2, a1), t21 = cz_mul_conj(mb2, b1), t22 = Cz{a2.re, -a2.im};
+    set(0, cz_mul(a2, a1));
+    set(1, cz_mul(a2, b1));
+    set(2, b2);
+    set(3, rot_top(a3, b3, t10, t20));
+    set(4, rot_top(a3, b3, t11, t21));
+    set(5, cz_mul(b3, t22));
+    set(6, rot_bottom(a3, b3, t10, t20));
+    set(7, rot_bottom(a3, b3, t11, t21));
+    set(8, cz_mul_conj(a3, t22));
 
+    // the links' places are worked out again from the five half indices: kept,
+    // the eight 64-bit offsets hold 16 registers through the solves (float
+    // 18-real: 266 registers with them, 237 without, i.e. two waves per SIMD)
+    asm("" : "+v"(h));
+#pragma unroll
+    for (int mu = 0; mu < 4; mu++) asm("" : "+v"(nb.hb[mu]));
 #pragma unroll
     for (int k = 0; k < L; k++) {
         Mat<R> o;
@@ -210,27 +257,38 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
             apply_left(w[k], G, o);
         }
         if constexpr (RU) reunitarise(o);
-        store_link<R, NE, NT>(o, U, off[k]);
+        store_link<R, NE, NT>(o, U, slot_off(k));
     }
 }
 
-// Waves per SIMD the compiler is asked to leave room for in the float
-// 8-real sweep (decoding and encoding make its compute phase the longest of
-// the storage forms); every other form fits one wave's registers.
-#ifndef GF_SWEEP8_WAVES
-#define GF_SWEEP8_WAVES 2
-#endif
+// Waves per SIMD the compiler is asked to leave room for: what each form
+// reaches without spilling. Fields that fit the last-level cache run at the
+// rate at which waves in their solves leave memory idle, so a second (third)
+// wave pays there: float 18-real at 22x18x26x30, one lane per site, one wave
+// 36.3 us, two waves 31.6 us.
+template <typename R, int NE, int LPS>
+constexpr int sweep_waves() {
+    if (sizeof(R) == 4) return LPS == 1 ? 2 : LPS == 2 ? 3 : 4;
+    return LPS == 1 ? 1 : 2;
+}
 
 // One workgroup per tile of blockDim/LPS sites of one member. (A persistent
 // grid-stride form was measured to double the register footprint, since
 // loop-invariant state stays live across the tile loop, so every tile gets
 // its own workgroup; the dispatcher balances the tiles over the CUs.)
 template <typename R, int NE, int LPS, bool NT, bool RU>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((NE == 4 && sizeof(R) == 4) ? GF_SWEEP8_WAVES : 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sweep_waves<R, NE, LPS>())))
 k_half_sweep(const CfgDesc *__restrict__ desc, const int *__restrict__ tile_cfg,
              const int *__restrict__ active, int parity, int order) {
-    // the tile order is a schedule choice: every tile is independent
-    const int tile = order ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    // The tile order is a schedule choice: every tile is independent. The odd
+    // half-sweep takes the tiles from the other end, so that it starts on the
+    // links that the even one touched last, still in the last-level cache
+    // (256 MB), and the next even one on those of the odd one. Half-sweep at
+    // 40^4 in float (737 MB) 276 -> 248 us, at 32^4 in double (604 MB)
+    // 212 -> 194 us. Counted within each XCD, so that a field that fits the
+    // L2s meets every tile on the XCD that held it.
+    const int b = parity ? xcd_reverse(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int tile = order ? xcd_tile(b, gridDim.x) : b;
     const int c = tile_cfg[tile];
     if (!active[c]) return;
     const CfgDesc d = desc[c];
@@ -244,10 +302,10 @@ static hipError_t launch_t(const Schedule &s, const CfgDesc *d_desc, const int *
                            const int *d_active, int ntiles, int parity, int reunit, hipStream_t st) {
     if (ntiles <= 0) return hipSuccess;
     if (reunit)
-        hipLaunchKernelGGL((k_half_sweep<R, NE, LPS, NT, true>), dim3(ntiles), dim3(s.block), 0, st,
+        hipLaunchKernelGGL((k_half_sweep<R, NE, LPS, NT, true>), dim3(ntiles), dim3(s.block), s.lds, st,
                            d_desc, d_tile_cfg, d_active, parity, s.order);
     else
-        hipLaunchKernelGGL((k_half_sweep<R, NE, LPS, NT, false>), dim3(ntiles), dim3(s.block), 0, st,
+        hipLaunchKernelGGL((k_half_sweep<R, NE, LPS, NT, false>), dim3(ntiles), dim3(s.block), s.lds, st,
                            d_desc, d_tile_cfg, d_active, parity, s.order);
     return hipGetLastError();
 }

@@ -15,6 +15,14 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int n) {
     return x * q + min(x, r) + i;
 }
 
+// Workgroup b of n, counted from the other end among the workgroups of its
+// XCD (a bijection of [0, n) that keeps every id on its XCD).
+__host__ __device__ __forceinline__ int xcd_reverse(int b, int n) {
+    constexpr int NX = 8;
+    const int x = b % NX, i = b / NX;
+    return ((n - x + NX - 1) / NX - 1 - i) * NX + x;
+}
+
 // Slab order for the kernels whose sites read their neighbours' data
 // (F/theta, the gauge transformation, the differentiation kernels). Their
 // tiles are runs of consecutive half indices h; the neighbour one step in t
