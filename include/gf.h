@@ -175,7 +175,8 @@ size_t gf_field_bytes(const gf_ctx *ctx, int member);
 
 /* Convert member 0's field between the canonical layout U_aos (device) and
  * the internal layout U (device). 12-real storage drops row 2 on pack and
- * rebuilds it on unpack. Asynchronous. */
+ * rebuilds it on unpack. Packing zeroes the padding of each parity's last
+ * block. Asynchronous. */
 int gf_pack(gf_ctx *ctx, const void *U_aos, void *U);
 int gf_unpack(gf_ctx *ctx, const void *U, void *U_aos);
 

@@ -15,6 +15,7 @@
 //
 // Also here: pack/unpack between the canonical [site][mu][N][N] layout and
 // the blocked layout, and standalone reunitarisation.
+#include "pack_tile.hpp"
 #include "sun_device.hpp"
 #include "sun_internal.hpp"
 
@@ -233,21 +234,30 @@ hipError_t launch_sun_lps(const Schedule &s, const CfgDesc *d_desc, const int *d
 }
 
 // Canonical AoS [site][mu][N][N] <-> blocked layout; one thread per link.
-template <typename R, int N>
-__global__ void __launch_bounds__(256) k_sun_pack(Geom g, const typename V2<R>::type *__restrict__ src,
-                           typename V2<R>::type *__restrict__ dst, int to_aos) {
-    const long long l = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= 4LL * g.V) return;
-    const int s = (int)(l >> 2), mu = (int)(l & 3);
-    const int x = s % g.nx, y = (s / g.nx) % g.ny, z = (s / (g.nx * g.ny)) % g.nz, t = s / (g.nx * g.ny * g.nz);
-    int p, h;
-    site_to_ph(g, x, y, z, t, p, h);
-    const long long o = link_off(g, mu, p, h);
+template <typename R, int N, bool UNPACK>
+__global__ void __launch_bounds__(PACK_BLOCK) k_sun_pack(Geom g, typename V2<R>::type *__restrict__ aos,
+                                                         typename V2<R>::type *__restrict__ U) {
+    typedef typename V2<R>::type v2;
+    constexpr int E = N * N;
+    typedef PackTile<v2, 4 * E> T;
+    __shared__ v2 lds[T::SIZE];
+    const int h0 = (int)blockIdx.x * T::TH;
+    const int sites = 2 * max(0, min(T::TH, g.Vh - h0));
+    v2 *run = aos + 8LL * E * h0;
+    if (!UNPACK) T::fill(lds, run, sites);
 #pragma unroll
-    for (int e = 0; e < N * N; e++) {
-        if (to_aos) dst[l * (N * N) + e] = src[o + (long long)e * BLK];
-        else dst[o + (long long)e * BLK] = src[l * (N * N) + e];
+    for (int l = threadIdx.x; l < 8 * T::TH; l += PACK_BLOCK) {
+        const int q = l / T::TH, h = l % T::TH, p = q >> 2, mu = q & 3;
+        const bool in = 2 * h < sites;
+        v2 *at = lds + (pack_side(g, p, h0 + h) * T::TH + h) * T::STRIDE + E * mu;
+        v2 *field = U + link_off(g, mu, p, h0 + h);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            if (!UNPACK) field[e * BLK] = in ? at[e] : v2{R(0), R(0)};
+            else if (in) at[e] = field[e * BLK];
+        }
     }
+    if (UNPACK) T::drain(lds, run, sites);
 }
 
 // Standalone reunitarisation of every link; one thread per link.
@@ -281,17 +291,15 @@ hipError_t launch_sun_half_sweep(int prec, int nc, const Schedule &s, const CfgD
 
 hipError_t launch_sun_pack(int prec, int nc, const Geom &g, const void *aos, void *U, int to_aos,
                            hipStream_t st) {
-    const long long n = 4LL * g.V;
-    const int B = 256;
-    const dim3 grid((unsigned)((n + B - 1) / B));
-#define GF_P(R, N)                                                                                 \
-    hipLaunchKernelGGL((k_sun_pack<R, N>), grid, dim3(B), 0, st, g,                                \
-                       (const V2<R>::type *)(to_aos ? U : aos), (V2<R>::type *)(to_aos ? aos : U), \
-                       to_aos)
+#define GF_U(R, N, UN)                                                                               \
+    hipLaunchKernelGGL((k_sun_pack<R, N, UN>), dim3(g.nb * (BLK / PackTile<V2<R>::type, 4 * N * N>::TH)), \
+                       dim3(PACK_BLOCK), 0, st, g, (V2<R>::type *)aos, (V2<R>::type *)U)
+#define GF_P(R, N) do { if (to_aos) GF_U(R, N, true); else GF_U(R, N, false); } while (0)
     if (nc == 2) { if (prec == 0) GF_P(double, 2); else GF_P(float, 2); }
     else if (nc == 4) { if (prec == 0) GF_P(double, 4); else GF_P(float, 4); }
     else return hipErrorInvalidValue;
 #undef GF_P
+#undef GF_U
     return hipGetLastError();
 }
 

@@ -213,10 +213,12 @@ class Context:
     def blocks(self, i=0):
         return (self.volume(i) // 2 + self.BLOCK - 1) // self.BLOCK
 
+    def _field_shape(self, i=0):
+        return (2, self.blocks(i), 4, self.nelem, self.BLOCK, 2)
+
     def empty_field(self, i=0, device="cuda") -> torch.Tensor:
         # zero-filled, so the padding of the last block is deterministic
-        return torch.zeros((2, self.blocks(i), 4, self.nelem, self.BLOCK, 2), dtype=self.rdtype,
-                           device=device)
+        return torch.zeros(self._field_shape(i), dtype=self.rdtype, device=device)
 
     def _check_field(self, U, i=0):
         n = 2 * self.blocks(i) * 4 * self.nelem * self.BLOCK * 2
@@ -235,7 +237,8 @@ class Context:
         if tuple(U_aos.shape) != self._canonical_shape():
             raise ValueError(f"canonical field must have shape {self._canonical_shape()}")
         if U is None:
-            U = self.empty_field(device=U_aos.device)
+            # packing writes every value, the padding of the last block included
+            U = torch.empty(self._field_shape(), dtype=self.rdtype, device=U_aos.device)
         self._check(lib.gf_pack(self._h, ctypes.c_void_p(_ptr(U_aos)),
                                 ctypes.c_void_p(self._check_field(U))))
         return U
@@ -354,7 +357,7 @@ class Context:
         return _ptr(s)
 
     def pack_alg(self, s_aos):
-        s = self.empty_alg(device=s_aos.device)
+        s = torch.empty((2, self.blocks(), 8, 64), dtype=self.rdtype, device=s_aos.device)
         if s_aos.dtype != self.rdtype or s_aos.numel() != 8 * self.volume():
             raise ValueError("canonical algebra field must be (nt, nz, ny, nx, 8) of the context dtype")
         self._check(lib.gf_pack_alg(self._h, ctypes.c_void_p(_ptr(s_aos)), ctypes.c_void_p(self._check_alg(s))))
