@@ -3,6 +3,7 @@
 // (with hipGraph replay of a check period), the schedule autotuner and
 // kernel timing. All device work goes to the context's stream.
 #include <hip/hip_runtime.h>
+#include <sched.h>
 
 #include <algorithm>
 #include <chrono>
@@ -52,12 +53,14 @@ struct gf_ctx {
     SlabOrder qslab{0, 0, 0, 0, 0};  // quality tile order (single lattices only)
     bool qstream = false;            // F/theta by k_quality_tstream (single SU(3) lattices)
     double *d_partials = nullptr;
-    double *d_result = nullptr;      // 2 per member
-    int *d_active = nullptr;         // per member (batch driver)
+    int *d_active = nullptr;         // per member (fix drivers)
     int *d_ones = nullptr;           // per member, all 1 (plain calls)
     int *d_iters = nullptr;
-    double *h_result = nullptr;      // pinned: 2n results
-    int *h_flags = nullptr;          // pinned: n active, n iters, n ones
+    int *d_count = nullptr;          // checks published to the ring
+    double *h_result = nullptr;      // pinned, written by the kernels: 2n results
+    int *h_flags = nullptr;          // pinned: n active, n iters (written by the kernels), n ones, n zeros, 1 count
+    CheckRec *ring = nullptr;        // pinned, written by the kernels: last checks of a single lattice
+    int checks = 0;                  // checks taken from the ring
     Schedule sched{};
     long long sweeps_done = 0;
     std::string err;
@@ -366,23 +369,29 @@ int quality_launch(gf_ctx *ctx, const int *d_active, int update, int swept, doub
     else
         HIPTRY(ctx, launch_sun_quality(ctx->prec, ctx->nc, ctx->d_desc, ctx->d_qtile_cfg, d_active,
                                        ctx->nqtiles, ctx->d_partials, ctx->qslab, st));
-    HIPTRY(ctx, launch_quality_final_nc(ctx->nc, ctx->d_desc, ctx->n, ctx->d_partials, ctx->d_result,
-                                        update ? ctx->d_active : nullptr, ctx->d_iters, swept, eps,
-                                        update, st));
+    // pinned memory has one address on host and device
+    const QualityOut out{ctx->h_result, update ? ctx->d_active : nullptr, ctx->d_iters, ctx->h_flags,
+                         ctx->n == 1 ? ctx->ring : nullptr, ctx->d_count};
+    HIPTRY(ctx, launch_quality_final(ctx->nc, ctx->d_desc, ctx->n, ctx->d_partials, out, swept, eps, st));
     return GF_OK;
 }
 
-// Copy results (and, for the batch driver, the flags) to pinned memory and wait.
-int read_back(gf_ctx *ctx, bool flags) {
-    HIPTRY(ctx, hipMemcpyAsync(ctx->h_result, ctx->d_result, 2 * ctx->n * sizeof(double),
-                               hipMemcpyDeviceToHost, ctx->stream));
-    if (flags) {
-        HIPTRY(ctx, hipMemcpyAsync(ctx->h_flags, ctx->d_active, ctx->n * sizeof(int),
-                                   hipMemcpyDeviceToHost, ctx->stream));
-        HIPTRY(ctx, hipMemcpyAsync(ctx->h_flags + ctx->n, ctx->d_iters, ctx->n * sizeof(int),
-                                   hipMemcpyDeviceToHost, ctx->stream));
+// Wait for check number `seq` of a single lattice: its record's number is
+// written last. The stream is asked now and then, so that a failed launch
+// ends the wait.
+int wait_check(gf_ctx *ctx, int seq, CheckRec *out) {
+    const CheckRec *r = ctx->ring + (seq - 1) % CHECK_RING;
+    for (long long spin = 0; __atomic_load_n(&r->seq, __ATOMIC_ACQUIRE) != seq; spin++) {
+        if (spin % 1024 != 1023) continue;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipErrorNotReady) {
+            if (spin > 200000) sched_yield();  // a long period: let other threads run
+            continue;
+        }
+        HIPTRY(ctx, e);
+        CHECK(ctx, __atomic_load_n(&r->seq, __ATOMIC_ACQUIRE) == seq, GF_EDEVICE, "a check's result is missing");
     }
-    HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
+    *out = *r;
     return GF_OK;
 }
 
@@ -456,18 +465,20 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
     if (hipMalloc(&ctx->d_desc, n * sizeof(CfgDesc)) != hipSuccess ||
         hipMalloc(&ctx->d_qtile_cfg, nq * sizeof(int)) != hipSuccess ||
         hipMalloc(&ctx->d_partials, 2 * (size_t)nq * sizeof(double)) != hipSuccess ||
-        hipMalloc(&ctx->d_result, 2 * n * sizeof(double)) != hipSuccess ||
         hipMalloc(&ctx->d_active, n * sizeof(int)) != hipSuccess ||
         hipMalloc(&ctx->d_ones, n * sizeof(int)) != hipSuccess ||
         hipMalloc(&ctx->d_iters, n * sizeof(int)) != hipSuccess ||
+        hipMalloc(&ctx->d_count, sizeof(int)) != hipSuccess ||
         hipHostMalloc(&ctx->h_stage, n * sizeof(CfgDesc), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(&ctx->h_result, 2 * n * sizeof(double), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&ctx->h_flags, 3 * n * sizeof(int), hipHostMallocDefault) != hipSuccess)
+        hipHostMalloc(&ctx->h_flags, (4 * n + 1) * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(&ctx->ring, CHECK_RING * sizeof(CheckRec), hipHostMallocDefault) != hipSuccess)
         return bail(GF_ENOMEM);
     if (hipEventCreateWithFlags(&ctx->stage_evt, hipEventDisableTiming) != hipSuccess ||
         hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking) != hipSuccess)
         return bail(GF_EDEVICE);
-    for (int c = 0; c < n; c++) ctx->h_flags[2 * n + c] = 1;
+    for (int c = 0; c < n; c++) { ctx->h_flags[2 * n + c] = 1; ctx->h_flags[3 * n + c] = 0; }
+    std::memset(ctx->ring, 0, CHECK_RING * sizeof(CheckRec));
     if (hipMemcpy(ctx->d_ones, ctx->h_flags + 2 * n, n * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(ctx->d_active, ctx->h_flags + 2 * n, n * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(ctx->d_qtile_cfg, qmap.data(), nq * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
@@ -535,10 +546,10 @@ int gf_destroy(gf_ctx *ctx) {
     (void)hipFree(ctx->d_tile_cfg);
     (void)hipFree(ctx->d_qtile_cfg);
     (void)hipFree(ctx->d_partials);
-    (void)hipFree(ctx->d_result);
     (void)hipFree(ctx->d_active);
     (void)hipFree(ctx->d_ones);
     (void)hipFree(ctx->d_iters);
+    (void)hipFree(ctx->d_count);
     (void)hipFree(ctx->d_spec);
     (void)hipFree(ctx->d_roots);
     (void)hipFree(ctx->d_gfield);
@@ -547,6 +558,7 @@ int gf_destroy(gf_ctx *ctx) {
     if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     if (ctx->h_result) (void)hipHostFree(ctx->h_result);
     if (ctx->h_flags) (void)hipHostFree(ctx->h_flags);
+    if (ctx->ring) (void)hipHostFree(ctx->ring);
     (void)hipFree(ctx->d_slice_part);
     (void)hipFree(ctx->d_slice_out);
     if (ctx->log) std::fclose(ctx->log);
@@ -634,7 +646,7 @@ int gf_batch_quality(gf_ctx *ctx, void *const *U, double *F, double *theta) {
     DeviceGuard dg(ctx->device);
     if ((rc = set_fields(ctx, U, nullptr))) return rc;
     if ((rc = quality_launch(ctx, nullptr, 0, 0, 0.0, ctx->stream))) return rc;
-    if ((rc = read_back(ctx, false))) return rc;
+    HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
     int bad = 0;
     for (int c = 0; c < ctx->n; c++) {
         F[c] = ctx->h_result[2 * c];
@@ -713,11 +725,11 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
     log_open(ctx);
     ctx->log_calls++;
     // every member starts active with zero sweeps
-    for (int c = 0; c < n; c++) { ctx->h_flags[c] = 1; ctx->h_flags[n + c] = 0; }
-    HIPTRY(ctx, hipMemcpyAsync(ctx->d_active, ctx->h_flags, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
-    HIPTRY(ctx, hipMemcpyAsync(ctx->d_iters, ctx->h_flags + n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    HIPTRY(ctx, hipMemcpyAsync(ctx->d_active, ctx->h_flags + 2 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    HIPTRY(ctx, hipMemcpyAsync(ctx->d_iters, ctx->h_flags + 3 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    ctx->h_flags[4 * n] = ctx->checks;
+    HIPTRY(ctx, hipMemcpyAsync(ctx->d_count, ctx->h_flags + 4 * n, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
     if ((rc = quality_launch(ctx, ctx->d_active, 1, 0, eps, ctx->stream))) return rc;
-    if ((rc = read_back(ctx, true))) return rc;
     // members active before a check (those whose result it refreshed)
     std::vector<int> was_active(n, 1);
     auto log_members = [&]() {
@@ -728,51 +740,90 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         log_flush(ctx);
         for (int c = 0; c < n; c++) was_active[c] = ctx->h_flags[c];
     };
-    log_members();
     const bool graphs = ctx->p.use_graph && !ctx->p.timing && ctx->p.check_every <= 64;
-    int it = 0;
-    auto any_active = [&]() {
-        for (int c = 0; c < n; c++) if (ctx->h_flags[c]) return true;
-        return false;
+    // one check period of m sweeps and its check, enqueued
+    auto period = [&](int m) -> int {
+        int r;
+        if (!graphs) {
+            if ((r = full_sweeps(ctx, m, ctx->d_active, ctx->stream))) return r;
+            return quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->stream);
+        }
+        unsigned long long pattern = 0;
+        for (int k = 1; k <= m; k++)
+            if (reunit_due(ctx, ctx->sweeps_done + k)) pattern |= 1ULL << (k - 1);
+        unsigned long long eps_bits;
+        std::memcpy(&eps_bits, &eps, sizeof eps_bits);
+        auto key = std::make_tuple(m, pattern, eps_bits);
+        auto f = ctx->graphs.find(key);
+        if (f == ctx->graphs.end()) {
+            hipGraph_t g;
+            hipGraphExec_t ge;
+            const long long keep = ctx->sweeps_done;
+            HIPTRY(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
+            int r1 = full_sweeps(ctx, m, ctx->d_active, ctx->cap_stream);
+            int r2 = r1 ? r1 : quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->cap_stream);
+            hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &g);
+            ctx->sweeps_done = keep;
+            if (r2) return r2;
+            HIPTRY(ctx, ec);
+            HIPTRY(ctx, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
+            f = ctx->graphs.emplace(key, std::make_pair(g, ge)).first;
+        }
+        HIPTRY(ctx, hipGraphLaunch(f->second.second, ctx->stream));
+        ctx->sweeps_done += m;
+        return GF_OK;
     };
     auto nonfinite = [&]() {
         for (int c = 0; c < n; c++)
             if (!std::isfinite(ctx->h_result[2 * c]) || !std::isfinite(ctx->h_result[2 * c + 1])) return true;
         return false;
     };
-    while (it < max_iter && any_active() && !nonfinite()) {
-        const int m = std::min(ctx->p.check_every, max_iter - it);
-        if (graphs) {
-            unsigned long long pattern = 0;
-            for (int k = 1; k <= m; k++)
-                if (reunit_due(ctx, ctx->sweeps_done + k)) pattern |= 1ULL << (k - 1);
-            unsigned long long eps_bits;
-            std::memcpy(&eps_bits, &eps, sizeof eps_bits);
-            auto key = std::make_tuple(m, pattern, eps_bits);
-            auto f = ctx->graphs.find(key);
-            if (f == ctx->graphs.end()) {
-                hipGraph_t g;
-                hipGraphExec_t ge;
-                const long long keep = ctx->sweeps_done;
-                HIPTRY(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
-                int r1 = full_sweeps(ctx, m, ctx->d_active, ctx->cap_stream);
-                int r2 = r1 ? r1 : quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->cap_stream);
-                hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &g);
-                ctx->sweeps_done = keep;
-                if (r2) return r2;
-                HIPTRY(ctx, ec);
-                HIPTRY(ctx, hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
-                f = ctx->graphs.emplace(key, std::make_pair(g, ge)).first;
+    if (n == 1) {
+        // The host stays one period ahead of the check it waits for: a check
+        // that ends the run retires the lattice on the device, and the period
+        // already enqueued finds it retired and does nothing. Only for short
+        // periods, whose launches and read-back the GPU would wait for (4^4
+        // with a check every sweep: 38 us a sweep without, RUNAHEAD us with);
+        // a long one's launches hide behind the period itself.
+        const bool ahead = !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
+        const long long sweeps0 = ctx->sweeps_done;
+        int enqueued = 0, pending = 1;
+        CheckRec k{};
+        for (;;) {
+            while (pending < (ahead ? 2 : 1) && enqueued < max_iter) {
+                const int m = std::min(ctx->p.check_every, max_iter - enqueued);
+                if ((rc = period(m))) return rc;
+                enqueued += m;
+                pending++;
             }
-            HIPTRY(ctx, hipGraphLaunch(f->second.second, ctx->stream));
-            ctx->sweeps_done += m;
-        } else {
-            if ((rc = full_sweeps(ctx, m, ctx->d_active, ctx->stream))) return rc;
-            if ((rc = quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->stream))) return rc;
+            if (pending == 0) break;
+            if ((rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
+            ctx->checks++;
+            pending--;
+            ctx->h_result[0] = k.F;
+            ctx->h_result[1] = k.theta;
+            ctx->h_flags[0] = k.active;
+            ctx->h_flags[1] = k.iters;
+            log_members();
+            if (!k.active) break;
         }
-        it += m;
-        if ((rc = read_back(ctx, true))) return rc;
+        ctx->sweeps_done = sweeps0 + k.iters;
+        HIPTRY(ctx, hipStreamSynchronize(ctx->stream));  // the call returns with its stream idle
+    } else {
+        HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
         log_members();
+        int it = 0;
+        auto any_active = [&]() {
+            for (int c = 0; c < n; c++) if (ctx->h_flags[c]) return true;
+            return false;
+        };
+        while (it < max_iter && any_active() && !nonfinite()) {
+            const int m = std::min(ctx->p.check_every, max_iter - it);
+            if ((rc = period(m))) return rc;
+            it += m;
+            HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
+            log_members();
+        }
     }
     bool all = true;
     for (int c = 0; c < n; c++) {

@@ -148,9 +148,6 @@ hipError_t launch_half_sweep(int prec, int nelem, const Schedule &s, const CfgDe
 hipError_t launch_quality(int prec, int nelem, const CfgDesc *d_desc, const int *d_qtile_cfg,
                           const int *d_active, int nqtiles, double *d_partials, const SlabOrder &so,
                           hipStream_t st);
-hipError_t launch_quality_final(const CfgDesc *d_desc, int n, const double *d_partials,
-                                double *d_result, int *d_active, int *d_iters, int swept,
-                                double eps, int update_active, hipStream_t st);
 // Per-time-slice F_t and theta_t of one member into d_out[2 t], d_out[2 t + 1];
 // d_partials holds 2 * nt * quality_slice_chunks(g) doubles.
 int quality_slice_chunks(const Geom &g);

@@ -17,9 +17,28 @@ hipError_t launch_sun_reunit(int prec, int nc, const Geom &g, void *U, hipStream
 hipError_t launch_sun_quality(int prec, int nc, const CfgDesc *d_desc, const int *d_qtile_cfg,
                               const int *d_active, int nqtiles, double *d_partials, const SlabOrder &so,
                               hipStream_t st);
-// k_quality_final with F and theta normalised for nc colours.
-hipError_t launch_quality_final_nc(int nc, const CfgDesc *d_desc, int n, const double *d_partials,
-                                   double *d_result, int *d_active, int *d_iters, int swept, double eps,
-                                   int update_active, hipStream_t st);
+// Where the final reduction leaves its results. All but iters, active and
+// count are pinned host memory, written by the kernel itself: reading a check
+// back then takes no copies, only the wait for it.
+struct CheckRec {       // one finished check of a single lattice's fix driver
+    double F, theta;
+    int active, iters;
+    int seq;            // number of the check, written last
+    int pad;
+};
+constexpr int CHECK_RING = 8;
+
+struct QualityOut {
+    double *result;     // 2 per member: F, theta
+    int *active;        // device: per member, 1 until theta < eps or not finite (null: plain evaluation)
+    int *iters;         // device: per member, sweeps so far
+    int *flags;         // pinned copies of active (n) and iters (n)
+    CheckRec *ring;     // null, or CHECK_RING records: check k goes to record (k - 1) mod CHECK_RING
+    int *count;         // device: checks published so far
+};
+
+// F and theta of every member from its partials, normalised for nc colours.
+hipError_t launch_quality_final(int nc, const CfgDesc *d_desc, int n, const double *d_partials,
+                                const QualityOut &out, int swept, double eps, hipStream_t st);
 
 }  // namespace gf
