@@ -76,7 +76,7 @@ struct gf_ctx {
     double *d_fout = nullptr;
     // Fourier-accelerated steepest descent: the half spectrum of the su(3)
     // components of Delta, and the tables of roots of unity for the x, y, z
-    // and t lengths (FFT_MAX_N complex doubles each)
+    // and t lengths (FFT_MAX_N complex doubles each), then their 4 sin^2(pi m / L)
     void *d_spec = nullptr;
     void *d_roots = nullptr;
     // per-time-slice quality: partials and results
@@ -1104,11 +1104,12 @@ int sd_prepare(gf_ctx *ctx) {
     }
     if (!ctx->d_roots) {
         void *w = nullptr;
-        if (hipMalloc(&w, 4 * (size_t)FFT_MAX_N * 16) != hipSuccess)
+        if (hipMalloc(&w, 4 * (size_t)FFT_MAX_N * (16 + 8)) != hipSuccess)
             return fail(ctx, GF_ENOMEM, "cannot allocate the Fourier acceleration buffers");
         const int len[4] = {g.nx, g.ny, g.nz, g.nt};
         for (int a = 0; a < 4; a++) {
-            const hipError_t e = launch_fft_roots((char *)w + (size_t)a * FFT_MAX_N * 16, len[a], ctx->stream);
+            double *p2 = (double *)((char *)w + 4 * (size_t)FFT_MAX_N * 16) + (size_t)a * FFT_MAX_N;
+            const hipError_t e = launch_fft_roots((char *)w + (size_t)a * FFT_MAX_N * 16, p2, len[a], ctx->stream);
             if (e != hipSuccess) {
                 (void)hipFree(w);
                 return fail(ctx, GF_EDEVICE, "root tables: %s", hipGetErrorString(e));
@@ -1123,6 +1124,8 @@ const void *sd_roots(const gf_ctx *ctx, int axis) {
     return (const char *)ctx->d_roots + (size_t)axis * FFT_MAX_N * 16;
 }
 
+const double *sd_p2(const gf_ctx *ctx) { return (const double *)sd_roots(ctx, 4); }
+
 // One step of Alg. 2: Delta -> F (x, y, z and, for Landau, t) -> times
 // (alpha/2) p2max / p^2 / N -> F^-1 -> g = reunit(1 + X) -> U <- g U g^dagger.
 // Delta is formed in the forward x pass and g in the inverse one; the filter
@@ -1135,18 +1138,23 @@ int sd_step_impl(gf_ctx *ctx, void *U, double alpha) {
     const FftSite fx = make_fft_site(g);
     const FftAxis fy = make_fft_axis(g, 1, !landau);
     const FftAxis fz = make_fft_axis(g, 2, !landau);
+    const int last = landau ? 3 : 2;
     FftAxis flt = landau ? make_fft_axis(g, 3, false) : fz;
+    const FftLine ly = make_fft_line(g, 1), lz = make_fft_line(g, 2);
+    FftLine llt = make_fft_line(g, last);
     const double nfft = landau ? (double)g.V : (double)g.nx * g.ny * g.nz;
-    flt.scale = 0.5 * alpha / nfft;
-    flt.p2max = landau ? 16.0 : 12.0;
+    flt.scale = llt.scale = 0.5 * alpha / nfft;
+    flt.p2max = llt.p2max = landau ? 16.0 : 12.0;
     hipStream_t st = ctx->stream;
-    const void *wx = sd_roots(ctx, 0), *wy = sd_roots(ctx, 1), *wz = sd_roots(ctx, 2), *wt = sd_roots(ctx, 3);
-    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, gauge, g, fx, wx, U, ctx->d_spec, st));
-    HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, wy, ctx->d_spec, -1, 0, st));
-    if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, wz, ctx->d_spec, -1, 0, st));
-    HIPTRY(ctx, launch_fft_axis(ctx->prec, flt, landau ? wt : wz, ctx->d_spec, -1, 1, st));
-    if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, wz, ctx->d_spec, 1, 0, st));
-    HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, wy, ctx->d_spec, 1, 0, st));
+    const void *wx = sd_roots(ctx, 0), *wy = sd_roots(ctx, 1), *wz = sd_roots(ctx, 2);
+    const double *p2 = sd_p2(ctx);
+    void *spec = ctx->d_spec;
+    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, gauge, g, fx, wx, U, spec, st));
+    HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, ly, wy, p2, spec, 1, -1, 0, st));
+    if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, lz, wz, p2, spec, 2, -1, 0, st));
+    HIPTRY(ctx, launch_fft_axis(ctx->prec, flt, llt, sd_roots(ctx, last), p2, spec, last, -1, 1, st));
+    if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, lz, wz, p2, spec, 2, 1, 0, st));
+    HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, ly, wy, p2, spec, 1, 1, 0, st));
     HIPTRY(ctx, launch_sd_fx_gfield(ctx->prec, g, fx, wx, ctx->d_spec, ctx->d_gfield, st));
     HIPTRY(ctx, launch_gauge_transform(ctx->prec, ctx->nelem, g, U, ctx->d_gfield, st));
     return GF_OK;

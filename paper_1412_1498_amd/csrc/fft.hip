@@ -14,7 +14,11 @@
 // pass writes back the filtered field already transformed back along its own
 // axis.
 //
-// A workgroup loads a tile of pencils (for y, z, t: consecutive kx of one row,
+// Lengths that split into two factors of at most 13 are transformed by two
+// butterflies in registers with one trip through LDS between them
+// (k_fft_line; along x, where the tile sits in LDS anyway, lds_split_forward
+// and lds_split_inverse for factors of at most 8). Any other length: a
+// workgroup loads a tile of pencils (for y, z, t: consecutive kx of one row,
 // so every global access is a contiguous run) into LDS and transforms them by
 // the mixed-radix Stockham algorithm (radix 4, 2, 3, 5 butterflies in
 // registers, any larger prime by a direct sum), in place: one LDS read, one
@@ -137,6 +141,114 @@ __device__ __forceinline__ void bfly5(Cd *v) {
     v[3] = csub(r, w);
 }
 
+// 8 points as two of 4 and the twiddles exp(SIGN 2 pi i m / 8).
+template <int SIGN>
+__device__ __forceinline__ void bfly8(Cd *v) {
+    const double h = 0.70710678118654752440;
+    Cd e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    bfly4<SIGN>(e);
+    bfly4<SIGN>(o);
+    const Cd i1 = imul<SIGN>(o[1]), i3 = imul<SIGN>(o[3]);
+    o[1] = Cd{h * (o[1].x + i1.x), h * (o[1].y + i1.y)};
+    o[2] = imul<SIGN>(o[2]);
+    o[3] = Cd{h * (i3.x - o[3].x), h * (i3.y - o[3].y)};
+#pragma unroll
+    for (int k = 0; k < 4; k++) { v[k] = cadd(e[k], o[k]); v[k + 4] = csub(e[k], o[k]); }
+}
+
+// An odd number of points R: with the sums a_j = v_j + v_(R-j) and differences
+// b_j, X_k = v_0 + sum_j cos(2 pi j k / R) a_j + SIGN i sum_j sin(2 pi j k / R) b_j.
+template <int R> struct OddRoots;
+template <> struct OddRoots<7> {
+    static constexpr double c[4] = {1.0, 0.6234898018587335, -0.2225209339563144, -0.9009688679024191};
+    static constexpr double s[4] = {0.0, 0.7818314824680298, 0.9749279121818236, 0.4338837391175581};
+};
+template <> struct OddRoots<9> {
+    static constexpr double c[5] = {1.0, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084};
+    static constexpr double s[5] = {0.0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386,
+                                    0.3420201433256687};
+};
+template <> struct OddRoots<11> {
+    static constexpr double c[6] = {1.0, 0.8412535328311812, 0.41541501300188644, -0.14231483827328514,
+                                    -0.6548607339452851, -0.9594929736144974};
+    static constexpr double s[6] = {0.0, 0.5406408174555976, 0.9096319953545183, 0.9898214418809327,
+                                    0.7557495743542583, 0.28173255684142967};
+};
+template <> struct OddRoots<13> {
+    static constexpr double c[7] = {1.0, 0.8854560256532099, 0.5680647467311558, 0.12053668025532305,
+                                    -0.3546048870425356, -0.7485107481711011, -0.970941817426052};
+    static constexpr double s[7] = {0.0, 0.46472317204376856, 0.8229838658936564, 0.992708874098054,
+                                    0.9350162426854148, 0.6631226582407952, 0.23931566428755777};
+};
+
+template <int SIGN, int R>
+__device__ __forceinline__ void bfly_odd(Cd *v) {
+    constexpr int H = (R - 1) / 2;
+    Cd a[H + 1], b[H + 1];
+#pragma unroll
+    for (int j = 1; j <= H; j++) { a[j] = cadd(v[j], v[R - j]); b[j] = csub(v[j], v[R - j]); }
+    const Cd v0 = v[0];
+    Cd sum = v0;
+#pragma unroll
+    for (int j = 1; j <= H; j++) sum = cadd(sum, a[j]);
+    v[0] = sum;
+#pragma unroll
+    for (int k = 1; k <= H; k++) {
+        Cd p = v0, q = {0.0, 0.0};
+#pragma unroll
+        for (int j = 1; j <= H; j++) {
+            const int m = j * k % R, i = m <= H ? m : R - m;
+            const double c = OddRoots<R>::c[i], s = m <= H ? OddRoots<R>::s[i] : -OddRoots<R>::s[i];
+            p = Cd{fma(c, a[j].x, p.x), fma(c, a[j].y, p.y)};
+            q = Cd{fma(s, b[j].x, q.x), fma(s, b[j].y, q.y)};
+        }
+        q = imul<SIGN>(q);
+        v[k] = cadd(p, q);
+        v[R - k] = csub(p, q);
+    }
+}
+
+template <int SIGN, int R>
+__device__ __forceinline__ void bfly(Cd *v);
+
+// R = P Q points, P and Q without common factor, by the prime-factor map: input
+// (Q i + P j) mod R, output (e_P k + e_Q l) mod R with e_P = 1 mod P, 0 mod Q
+// and e_Q the other way round: no twiddles between the two.
+template <int SIGN, int P, int Q, int EP, int EQ>
+__device__ __forceinline__ void bfly_pfa(Cd *v) {
+    constexpr int R = P * Q;
+    static_assert(EP % P == 1 && EP % Q == 0 && EQ % Q == 1 && EQ % P == 0, "prime-factor map");
+    Cd t[Q][P];
+#pragma unroll
+    for (int j = 0; j < Q; j++)
+#pragma unroll
+        for (int i = 0; i < P; i++) t[j][i] = v[(Q * i + P * j) % R];
+#pragma unroll
+    for (int j = 0; j < Q; j++) bfly<SIGN, P>(t[j]);
+#pragma unroll
+    for (int k = 0; k < P; k++) {
+        Cd u[Q];
+#pragma unroll
+        for (int j = 0; j < Q; j++) u[j] = t[j][k];
+        bfly<SIGN, Q>(u);
+#pragma unroll
+        for (int l = 0; l < Q; l++) v[(EP * k + EQ * l) % R] = u[l];
+    }
+}
+
+template <int SIGN, int R>
+__device__ __forceinline__ void bfly(Cd *v) {
+    if constexpr (R == 2) bfly2<SIGN>(v);
+    else if constexpr (R == 3) bfly3<SIGN>(v);
+    else if constexpr (R == 4) bfly4<SIGN>(v);
+    else if constexpr (R == 5) bfly5<SIGN>(v);
+    else if constexpr (R == 6) bfly_pfa<SIGN, 2, 3, 3, 4>(v);
+    else if constexpr (R == 8) bfly8<SIGN>(v);
+    else if constexpr (R == 10) bfly_pfa<SIGN, 2, 5, 5, 6>(v);
+    else if constexpr (R == 12) bfly_pfa<SIGN, 4, 3, 9, 4>(v);
+    else bfly_odd<SIGN, R>(v);
+}
+
 // Butterflies per thread in a radix-R pass: a tile holds at most
 // FFT_TILE_POINTS points, i.e. FFT_TILE_POINTS / R butterflies, over
 // FFT_BLOCK threads; outputs per thread in a pass of any other radix.
@@ -168,10 +280,7 @@ __device__ __forceinline__ void stockham_pass(Cd *buf, const Cd *Wl, int n, int 
             for (int r = 0; r < R; r++) v[i][r] = buf[(j + r * nb) * ld + q];
 #pragma unroll
             for (int r = 1; r < R; r++) v[i][r] = cmul(v[i][r], root<SIGN>(Wl[r * k * tw]));
-            if constexpr (R == 2) bfly2<SIGN>(v[i]);
-            if constexpr (R == 3) bfly3<SIGN>(v[i]);
-            if constexpr (R == 4) bfly4<SIGN>(v[i]);
-            if constexpr (R == 5) bfly5<SIGN>(v[i]);
+            bfly<SIGN, R>(v[i]);
         }
     }
     __syncthreads();
@@ -235,6 +344,67 @@ __device__ __forceinline__ void lds_dft(const Tile &t, const FftPlan &pl, int n,
         Ns *= R;
     }
     __syncthreads();
+}
+
+// Two butterflies over np pencils held in LDS, n = n1 n2 (index n2 i + j, spectrum
+// k + n1 l), where the axis length splits so: three barriers instead of two a
+// radix, and no point is moved between its two reads. Forward: a lane
+// transforms the n1 points i of one j in place (place k n2 + j gets k), then
+// the n2 points j of one k; mode k + n1 l ends at place k n2 + l. Inverse: the
+// same backwards, from those places to natural order.
+#define GF_SITE_RADICES(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+
+// points at base + m step (m < R) of every pencil, for rows 0 .. rows - 1 whose
+// base is row * rstep; times W^(row m) before (PRE) or after the butterfly
+template <int SIGN, int R, bool PRE>
+__device__ __forceinline__ void lds_rows(const Tile &t, int rows, int rstep, int step, bool twiddle, int np) {
+    for (int idx = threadIdx.x; idx < rows * np; idx += blockDim.x) {
+        const int row = (int)fdiv((unsigned)idx, t.dnp), q = idx - row * np;
+        Cd *a = t.a + row * rstep * t.ld + q;
+        Cd v[R];
+#pragma unroll
+        for (int m = 0; m < R; m++) v[m] = a[m * step * t.ld];
+        if (PRE && twiddle) {
+#pragma unroll
+            for (int m = 1; m < R; m++) v[m] = cmul(v[m], root<SIGN>(t.Wl[row * m]));
+        }
+        bfly<SIGN, R>(v);
+#pragma unroll
+        for (int m = 0; m < R; m++)
+            a[m * step * t.ld] = (!PRE && twiddle && m) ? cmul(v[m], root<SIGN>(t.Wl[row * m])) : v[m];
+    }
+}
+
+// forward transform; begins and ends with a barrier
+__device__ __forceinline__ void lds_split_forward(const Tile &t, int n1, int n2, int np) {
+    __syncthreads();
+#define GF_S(r) case r: lds_rows<-1, r, false>(t, n2, 1, n2, true, np); break;
+    switch (n1) { GF_SITE_RADICES(GF_S) default: break; }
+#undef GF_S
+    __syncthreads();
+#define GF_S(r) case r: lds_rows<-1, r, false>(t, n1, n2, 1, false, np); break;
+    switch (n2) { GF_SITE_RADICES(GF_S) default: break; }
+#undef GF_S
+    __syncthreads();
+}
+
+// inverse transform; begins and ends with a barrier
+__device__ __forceinline__ void lds_split_inverse(const Tile &t, int n1, int n2, int np) {
+    __syncthreads();
+#define GF_S(r) case r: lds_rows<1, r, false>(t, n1, n2, 1, false, np); break;
+    switch (n2) { GF_SITE_RADICES(GF_S) default: break; }
+#undef GF_S
+    __syncthreads();
+#define GF_S(r) case r: lds_rows<1, r, true>(t, n2, 1, n2, true, np); break;
+    switch (n1) { GF_SITE_RADICES(GF_S) default: break; }
+#undef GF_S
+    __syncthreads();
+}
+
+// place of mode m of a split length
+__device__ __forceinline__ int split_place(const FftSite &f, int m) {
+    const int l = (int)fdiv((unsigned)m, f.dn1);
+    return (m - l * f.n1) * f.n2 + l;
 }
 
 __device__ __forceinline__ double lattice_p2(int k, int L) {
@@ -376,14 +546,17 @@ k_sd_delta_fx(Geom g, int nd, const typename V2<R>::type *__restrict__ Uv, FftSi
 #pragma unroll
         for (int c = 0; c < 4; c++) t.a[x * t.ld + yl * 4 + c] = Cd{o[2 * c], o[2 * c + 1]};
     }
-    lds_dft<-1>(t, f.pl, nx, nc);
+    if (f.n1) lds_split_forward(t, f.n1, f.n2, nc);
+    else lds_dft<-1>(t, f.pl, nx, nc);
     for (int idx = threadIdx.x; idx < 8 * f.ys * f.nkx; idx += blockDim.x) {
         const int row = (int)fdiv((unsigned)idx, f.dnkx), k = idx - row * f.nkx;
         const int yl = row >> 3, a = row & 7;
         const RowInfo r = ri[yl];
         if (r.zy < 0) continue;
         const int cr = yl * 4 + (a >> 1);
-        const Cd zk = t.a[k * t.ld + cr], zm = t.a[((nx - k) % nx) * t.ld + cr];
+        const int km = k ? nx - k : 0;
+        const Cd zk = t.a[(f.n1 ? split_place(f, k) : k) * t.ld + cr];
+        const Cd zm = t.a[(f.n1 ? split_place(f, km) : km) * t.ld + cr];
         typename V2<R>::type v;
         if (a & 1) {  // (zk - conj zm) / 2i
             v.x = (R)(0.5 * (zk.y + zm.y));
@@ -439,14 +612,17 @@ k_sd_fx_gfield(Geom g, FftSite f, const Cd *__restrict__ Wg, const typename V2<R
         const int cr = (int)fdiv((unsigned)idx, f.dnkx), k = idx - cr * f.nkx;
         const double z = ok[i] ? 1.0 : 0.0;
         const Cd A = Cd{z * (double)va[i].x, z * (double)va[i].y}, B = Cd{z * (double)vb[i].x, z * (double)vb[i].y};
+        const int pk = f.n1 ? split_place(f, k) : k;
         if (k == 0 || k == h) {
-            t.a[k * t.ld + cr] = Cd{A.x, B.x};
+            t.a[pk * t.ld + cr] = Cd{A.x, B.x};
         } else {
-            t.a[k * t.ld + cr] = Cd{A.x - B.y, A.y + B.x};
-            t.a[(nx - k) * t.ld + cr] = Cd{A.x + B.y, B.x - A.y};
+            const int pm = f.n1 ? split_place(f, nx - k) : nx - k;
+            t.a[pk * t.ld + cr] = Cd{A.x - B.y, A.y + B.x};
+            t.a[pm * t.ld + cr] = Cd{A.x + B.y, B.x - A.y};
         }
     }
-    lds_dft<1>(t, f.pl, nx, nc);
+    if (f.n1) lds_split_inverse(t, f.n1, f.n2, nc);
+    else lds_dft<1>(t, f.pl, nx, nc);
     for (int idx = threadIdx.x; idx < f.ys * nx; idx += blockDim.x) {
         const int yl = (int)fdiv((unsigned)idx, f.dn), x = idx - yl * nx;
         const RowInfo r = ri[yl];
@@ -543,13 +719,142 @@ k_fft_axis(FftAxis f, const Cd *__restrict__ Wg, typename V2<R>::type *__restric
     }
 }
 
-// W[m] = exp(2 pi i m / n), m < n.
-__global__ void __launch_bounds__(256) k_fft_roots(Cd *__restrict__ W, int n) {
+// One axis by two butterflies in registers: n = n1 n2, input index
+// n2 i + j, output index k + n1 l. A lane takes the n1 points i of one (j,
+// pencil) straight from memory, transforms them, multiplies by
+// W^(j k) and leaves them in LDS; after the one barrier a lane takes the n2
+// points j of one (k, pencil), transforms them and writes them back. With
+// FILTER they are scaled instead, transformed back in place (same lane, same
+// LDS places) and, after a second barrier, along i.
+// What bounds it: memory. The LDS kernel below moves every point through LDS
+// once a radix (4, 4, 3 at 48) and once more at either end, with a barrier
+// each, and its four workgroups a CU could not hide that: 3.0 TB/s in float.
+// A pass at 48^4, before -> after: float 119 -> 50-59 us (6-7 TB/s: the
+// spectrum fits the last-level cache), filtered 232 -> 77 us; double
+// 136 -> 119-124 us, filtered 249 -> 167 us. The LDS kernel stays for the
+// lengths that do not split (a prime factor above 13, or above 13^2).
+// Tiles are LINE_NP consecutive pencils, so that every access is a run of 256
+// bytes, aligned wherever the inner extent is a multiple of it.
+template <typename R> constexpr int LINE_NP = sizeof(R) == 4 ? 32 : 16;
+
+template <typename R>
+struct LineCtx {
+    const FftLine &f;
+    const Cd *W;
+    Cd *lds;
+    typename V2<R>::type *at;  // the lane's pencil
+    int q, row;                // pencil within the tile, the lane's j or k
+    bool in;                   // the pencil exists
+};
+
+// memory -> i-transform -> LDS
+template <typename R, int SIGN, int N1>
+__device__ __forceinline__ void line_first(const LineCtx<R> &c) {
+    const int n2 = c.f.n2, j = c.row;
+    if (j >= n2) return;
+    typename V2<R>::type x[N1];
+    Cd v[N1], w[N1];
+#pragma unroll
+    for (int i = 0; i < N1; i++) x[i] = c.at[(long long)(i * n2 + j) * c.f.s_ax];
+#pragma unroll
+    for (int k = 1; k < N1; k++) w[k] = c.W[j * k];
+#pragma unroll
+    for (int i = 0; i < N1; i++) v[i] = Cd{(double)x[i].x, (double)x[i].y};
+    bfly<SIGN, N1>(v);
+#pragma unroll
+    for (int k = 0; k < N1; k++)
+        c.lds[(k * n2 + j) * LINE_NP<R> + c.q] = k ? cmul(v[k], root<SIGN>(w[k])) : v[0];
+}
+
+// LDS -> j-transform -> memory, or filter and back to LDS
+template <typename R, int SIGN, bool FILTER, int N2>
+__device__ __forceinline__ void line_second(const LineCtx<R> &c, const double *p2ax, double p2) {
+    const int n1 = c.f.n1, k = c.row;
+    if (k >= n1) return;
+    Cd v[N2];
+    Cd *l = c.lds + k * N2 * LINE_NP<R> + c.q;
+#pragma unroll
+    for (int j = 0; j < N2; j++) v[j] = l[j * LINE_NP<R>];
+    bfly<SIGN, N2>(v);
+    if constexpr (!FILTER) {
+        if (!c.in) return;
+#pragma unroll
+        for (int i = 0; i < N2; i++)
+            c.at[(long long)(k + n1 * i) * c.f.s_ax] = typename V2<R>::type{(R)v[i].x, (R)v[i].y};
+    } else {
+        const double sp = c.f.scale * c.f.p2max;
+#pragma unroll
+        for (int i = 0; i < N2; i++) {
+            const double s = p2 + p2ax[k + n1 * i];
+            const double fac = s > 0.0 ? sp / s : 0.0;
+            v[i].x *= fac;
+            v[i].y *= fac;
+        }
+        bfly<1, N2>(v);
+#pragma unroll
+        for (int j = 0; j < N2; j++) l[j * LINE_NP<R>] = j ? cmul(v[j], c.W[j * k]) : v[0];
+    }
+}
+
+// LDS -> inverse i-transform -> memory
+template <typename R, int N1>
+__device__ __forceinline__ void line_third(const LineCtx<R> &c) {
+    const int n2 = c.f.n2, j = c.row;
+    if (j >= n2) return;
+    Cd v[N1];
+#pragma unroll
+    for (int k = 0; k < N1; k++) v[k] = c.lds[(k * n2 + j) * LINE_NP<R> + c.q];
+    bfly<1, N1>(v);
+    if (!c.in) return;
+#pragma unroll
+    for (int i = 0; i < N1; i++)
+        c.at[(long long)(i * n2 + j) * c.f.s_ax] = typename V2<R>::type{(R)v[i].x, (R)v[i].y};
+}
+
+// MAXR: largest radix (8, whose registers allow twice the waves, or 13).
+template <typename R, int SIGN, bool FILTER, int MAXR>
+__global__ void __launch_bounds__(MAXR * LINE_NP<R> > 256 ? 448 : 256)
+k_fft_line(FftLine f, const Cd *__restrict__ W, const double *__restrict__ p2, int axis,
+           typename V2<R>::type *__restrict__ spec) {
+    extern __shared__ Cd lds[];
+    constexpr int NP = LINE_NP<R>;
+    const int q = threadIdx.x % NP, row = threadIdx.x / NP;
+    const unsigned P = (unsigned)xcd_tile(blockIdx.x, gridDim.x) * NP + q;
+    const bool in = P < f.total;
+    const unsigned Pc = in ? P : 0u;  // lanes past the last pencil read pencil 0 and write nothing
+    const unsigned o = wdiv(Pc, f.dQ), inner = Pc - o * f.dQ.d;
+    const LineCtx<R> c{f, W, lds, spec + (long long)o * f.s_o + inner, q, row, in};
+    double p2p = 0.0;
+    if constexpr (FILTER) {
+        const unsigned yz = wdiv(inner, f.dkx), y0 = wdiv(yz, f.dy);
+        p2p = p2[inner - yz * f.dkx.d] + p2[FFT_MAX_N + yz - y0 * f.dy.d];
+        if (f.nz) p2p += p2[2 * FFT_MAX_N + (int)y0 % f.nz];
+    }
+#define GF_RADICES(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13)
+#define GF_R1(r) case r: if constexpr (r <= MAXR) line_first<R, SIGN, r>(c); break;
+    switch (f.n1) { GF_RADICES(GF_R1) default: break; }
+    __syncthreads();
+#define GF_R2(r) case r: if constexpr (r <= MAXR) line_second<R, SIGN, FILTER, r>(c, p2 + axis * FFT_MAX_N, p2p); break;
+    switch (f.n2) { GF_RADICES(GF_R2) default: break; }
+    if constexpr (FILTER) {
+        __syncthreads();
+#define GF_R3(r) case r: if constexpr (r <= MAXR) line_third<R, r>(c); break;
+        switch (f.n1) { GF_RADICES(GF_R3) default: break; }
+    }
+#undef GF_R1
+#undef GF_R2
+#undef GF_R3
+#undef GF_RADICES
+}
+
+// W[m] = exp(2 pi i m / n) and p2[m] = 4 sin^2(pi m / n), m < n.
+__global__ void __launch_bounds__(256) k_fft_roots(Cd *__restrict__ W, double *__restrict__ p2, int n) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n) return;
     double s, c;
     sincospi(2.0 * (double)m / (double)n, &s, &c);
     W[m] = Cd{c, s};
+    p2[m] = lattice_p2(m, n);
 }
 
 // Radices of a length: 4s first, then 2, 3, 5, then any other primes.
@@ -565,11 +870,36 @@ static FftPlan plan_length(int n) {
     return p;
 }
 
+// n = n1 n2 with n1 <= n2 <= rmax as close as they come (0, 0: none).
+static void split_length(int n, int rmax, int *n1, int *n2) {
+    *n1 = *n2 = 0;
+    for (int a = 2; a * a <= n; a++)
+        if (n % a == 0 && n / a <= rmax) { *n1 = a; *n2 = n / a; }
+}
+
+FftLine make_fft_line(const Geom &g, int axis) {
+    FftLine f{};
+    const long long nkx = g.nx / 2 + 1, sy = nkx, sz = g.ny * sy, sa = g.nz * sz, st = 8 * sa;
+    long long Q, outer;
+    if (axis == 1) { f.n = g.ny; f.s_ax = Q = sy; outer = (long long)g.nt * 8 * g.nz; f.s_o = sz; }
+    else if (axis == 2) { f.n = g.nz; f.s_ax = Q = sz; outer = (long long)g.nt * 8; f.s_o = sa; }
+    else { f.n = g.nt; f.s_ax = Q = st; outer = 1; f.s_o = 0; }
+    f.dQ = make_widediv((unsigned)Q);
+    f.total = (unsigned)(outer * Q);
+    f.dkx = make_widediv((unsigned)nkx);
+    f.dy = make_widediv((unsigned)g.ny);
+    f.nz = axis == 3 ? g.nz : 0;
+    split_length(f.n, FFT_LINE_RADIX, &f.n1, &f.n2);
+    return f;
+}
+
 FftSite make_fft_site(const Geom &g) {
     FftSite f;
     f.n = g.nx;
     f.nkx = g.nx / 2 + 1;
     f.pl = plan_length(f.n);
+    split_length(f.n, FFT_SITE_RADIX, &f.n1, &f.n2);
+    f.dn1 = make_fastdiv((unsigned)(f.n1 ? f.n1 : 1));
     f.ys = FFT_TILE_POINTS / (4 * g.nx);  // site rows per workgroup (>= 1: nx <= FFT_MAX_NX)
     f.srows = (long long)g.nt * g.nz * g.ny;
     f.dn = make_fastdiv((unsigned)f.n);
@@ -612,8 +942,8 @@ FftAxis make_fft_axis(const Geom &g, int axis, bool coulomb) {
 
 static size_t lds_bytes(int n, int np) { return (size_t)tile_lds_points(n, np) * sizeof(Cd); }
 
-hipError_t launch_fft_roots(void *W, int n, hipStream_t st) {
-    hipLaunchKernelGGL(k_fft_roots, dim3((n + 255) / 256), dim3(256), 0, st, (Cd *)W, n);
+hipError_t launch_fft_roots(void *W, double *p2, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_fft_roots, dim3((n + 255) / 256), dim3(256), 0, st, (Cd *)W, p2, n);
     return hipGetLastError();
 }
 
@@ -651,12 +981,32 @@ hipError_t launch_sd_fx_gfield(int prec, const Geom &g, const FftSite &f, const 
     return hipGetLastError();
 }
 
-hipError_t launch_fft_axis(int prec, const FftAxis &f, const void *W, void *spec, int sign, int filter,
-                           hipStream_t st) {
+template <typename R, int MAXR>
+static hipError_t launch_line(const FftLine &l, const Cd *w, const double *p2, void *spec, int axis, int sign,
+                              int filter, hipStream_t st) {
+    constexpr int NP = LINE_NP<R>;
+    const dim3 grid((l.total + NP - 1) / NP), block((l.n2 * NP + 63) / 64 * 64);  // n1 <= n2
+    const size_t sh = (size_t)l.n * NP * sizeof(Cd);
+    typename V2<R>::type *sp = (typename V2<R>::type *)spec;
+    if (filter) hipLaunchKernelGGL((k_fft_line<R, -1, true, MAXR>), grid, block, sh, st, l, w, p2, axis, sp);
+    else if (sign < 0) hipLaunchKernelGGL((k_fft_line<R, -1, false, MAXR>), grid, block, sh, st, l, w, p2, axis, sp);
+    else hipLaunchKernelGGL((k_fft_line<R, 1, false, MAXR>), grid, block, sh, st, l, w, p2, axis, sp);
+    return hipGetLastError();
+}
+
+hipError_t launch_fft_axis(int prec, const FftAxis &f, const FftLine &l, const void *W, const double *p2, void *spec,
+                           int axis, int sign, int filter, hipStream_t st) {
+    const Cd *w = (const Cd *)W;
+    if (l.n1) {
+        if (prec == 0)
+            return l.n2 <= 8 ? launch_line<double, 8>(l, w, p2, spec, axis, sign, filter, st)
+                             : launch_line<double, FFT_LINE_RADIX>(l, w, p2, spec, axis, sign, filter, st);
+        return l.n2 <= 8 ? launch_line<float, 8>(l, w, p2, spec, axis, sign, filter, st)
+                         : launch_line<float, FFT_LINE_RADIX>(l, w, p2, spec, axis, sign, filter, st);
+    }
     const dim3 grid((unsigned)((long long)f.r[0] * f.r[1] * f.r[2] * f.nchunk));
     // the filter's tables of the axis and kx terms (n + np doubles) follow the roots
     const size_t sh = lds_bytes(f.n, f.np) + (filter ? (size_t)(f.n + f.np) * sizeof(double) : 0);
-    const Cd *w = (const Cd *)W;
     const int sg = sign < 0 ? -1 : 1;
 #define GF_L(R, FL) \
     hipLaunchKernelGGL((k_fft_axis<R, FL>), grid, dim3(FFT_BLOCK), sh, st, f, w, (V2<R>::type *)spec, sg)
