@@ -293,8 +293,8 @@ int gf_unpack_alg(gf_ctx *ctx, const void *s, void *s_aos);
 int gf_functional(gf_ctx *ctx, const void *U, const void *s, double *F);
 
 /* grad = dF * dF_U[g]/ds_a(x) at s, in the layout of s: the su(3)-valued
- * gradient of eq. (1) with respect to the gauge transformation.
- * Asynchronous. */
+ * gradient of eq. (1) with respect to the gauge transformation; zeros in the
+ * padding. Asynchronous. */
 int gf_functional_grad(gf_ctx *ctx, const void *U, const void *s, double dF, void *grad);
 
 /* Apply g = exp(S(s)): U_mu(x) <- g(x) U_mu(x) g(x + mu)^dagger for all mu.

@@ -73,7 +73,6 @@ struct gf_ctx {
     // differentiation scratch: g field (9 complex per site) and partials
     void *d_gfield = nullptr;
     double *d_fpart = nullptr;
-    double *d_fout = nullptr;
     // Fourier-accelerated steepest descent: the half spectrum of the su(3)
     // components of Delta, and the tables of roots of unity for the x, y, z
     // and t lengths (FFT_MAX_N complex doubles each), then their 4 sin^2(pi m / L)
@@ -554,7 +553,6 @@ int gf_destroy(gf_ctx *ctx) {
     (void)hipFree(ctx->d_roots);
     (void)hipFree(ctx->d_gfield);
     (void)hipFree(ctx->d_fpart);
-    (void)hipFree(ctx->d_fout);
     if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     if (ctx->h_result) (void)hipHostFree(ctx->h_result);
     if (ctx->h_flags) (void)hipHostFree(ctx->h_flags);
@@ -1001,10 +999,6 @@ int ensure_diff_scratch(gf_ctx *ctx) {
         ctx->d_fpart = nullptr;
         return fail(ctx, GF_ENOMEM, "cannot allocate functional partials");
     }
-    if (!ctx->d_fout && hipMalloc(&ctx->d_fout, sizeof(double)) != hipSuccess) {
-        ctx->d_fout = nullptr;
-        return fail(ctx, GF_ENOMEM, "cannot allocate the functional result");
-    }
     return GF_OK;
 }
 
@@ -1052,8 +1046,7 @@ int gf_functional(gf_ctx *ctx, const void *U, const void *s, double *F) {
     const int nb = (g.V + 255) / 256;
     HIPTRY(ctx, launch_functional(ctx->prec, ctx->nelem, ctx->desc[0].gauge, g, U, ctx->d_gfield,
                                   ctx->d_fpart, ctx->stream));
-    HIPTRY(ctx, launch_sum_partials(ctx->d_fpart, nb, ctx->d_fout, ctx->stream));
-    HIPTRY(ctx, hipMemcpyAsync(ctx->h_result, ctx->d_fout, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    HIPTRY(ctx, launch_sum_partials(ctx->d_fpart, nb, ctx->h_result, ctx->stream));  // pinned: no copy
     HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
     const int nd = ctx->desc[0].gauge == GF_LANDAU ? 4 : 3;
     *F = ctx->h_result[0] / (nd * 3.0 * (double)g.V);

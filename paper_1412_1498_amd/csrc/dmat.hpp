@@ -54,21 +54,43 @@ __device__ __forceinline__ void dm_mul_nd(const DMat &a, const DMat &b, DMat &c)
         }
 }
 
-// a^dagger * b^dagger: element (i, j) = sum_k conj(a_ki) conj(b_jk)
-__device__ __forceinline__ void dm_mul_dd(const DMat &a, const DMat &b, DMat &c) {
+// c += a b^dagger and c += a^dagger b^dagger for stored matrices (float or
+// double, promoted as they are used), every element one FMA chain on c: no
+// product matrix is held besides the sum.
+template <typename R>
+__device__ __forceinline__ void dm_acc_nd(const Mat<R> &a, const Mat<R> &b, DMat &c) {
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
         for (int j = 0; j < 3; j++) {
-            double r = a.re[i] * b.re[3 * j], m = -a.re[i] * b.im[3 * j];
-            r = fma(-a.im[i], b.im[3 * j], r);
-            m = fma(-a.im[i], b.re[3 * j], m);
+            double r = c.re[3 * i + j], m = c.im[3 * i + j];
 #pragma unroll
-            for (int k = 1; k < 3; k++) {
-                r = fma(a.re[3 * k + i], b.re[3 * j + k], r);
-                r = fma(-a.im[3 * k + i], b.im[3 * j + k], r);
-                m = fma(-a.re[3 * k + i], b.im[3 * j + k], m);
-                m = fma(-a.im[3 * k + i], b.re[3 * j + k], m);
+            for (int k = 0; k < 3; k++) {
+                const double ar = a.re[3 * i + k], ai = a.im[3 * i + k], br = b.re[3 * j + k], bi = b.im[3 * j + k];
+                r = fma(ar, br, r);
+                r = fma(ai, bi, r);
+                m = fma(ai, br, m);
+                m = fma(-ar, bi, m);
+            }
+            c.re[3 * i + j] = r;
+            c.im[3 * i + j] = m;
+        }
+}
+
+template <typename R>
+__device__ __forceinline__ void dm_acc_dd(const Mat<R> &a, const Mat<R> &b, DMat &c) {
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            double r = c.re[3 * i + j], m = c.im[3 * i + j];
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const double ar = a.re[3 * k + i], ai = a.im[3 * k + i], br = b.re[3 * j + k], bi = b.im[3 * j + k];
+                r = fma(ar, br, r);
+                r = fma(-ai, bi, r);
+                m = fma(-ar, bi, m);
+                m = fma(-ai, br, m);
             }
             c.re[3 * i + j] = r;
             c.im[3 * i + j] = m;
@@ -79,6 +101,19 @@ __device__ __forceinline__ void dm_mul_dd(const DMat &a, const DMat &b, DMat &c)
 template <typename R>
 __device__ __forceinline__ void load_g(const typename V2<R>::type *__restrict__ gf, const Geom &g, int p, int h,
                                        DMat &m) {
+    const long long o = gfield_off(g, p, h, 0);
+#pragma unroll
+    for (int e = 0; e < 9; e++) {
+        typename V2<R>::type v = gf[o + (long long)e * BLK];
+        m.re[e] = v.x;
+        m.im[e] = v.y;
+    }
+}
+
+// the same as stored
+template <typename R>
+__device__ __forceinline__ void load_g(const typename V2<R>::type *__restrict__ gf, const Geom &g, int p, int h,
+                                       Mat<R> &m) {
     const long long o = gfield_off(g, p, h, 0);
 #pragma unroll
     for (int e = 0; e < 9; e++) {

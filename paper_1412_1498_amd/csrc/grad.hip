@@ -232,65 +232,124 @@ __device__ __forceinline__ void su3_components(const DMat &Y, double out[8]) {
 // (i, j, k; f) contributes w_i += f (s_k v_j - s_j v_k) and its cyclic
 // images. Nonzero f (generators numbered from 1): f_123 = 1,
 // f_147 = f_246 = f_257 = f_345 = 1/2, f_156 = f_367 = -1/2,
-// f_458 = f_678 = sqrt(3)/2.
-__device__ __forceinline__ void ad_triple(const double s[8], const double v[8], double w[8], int i, int j,
-                                          int k, double f) {
-    w[i] += f * (s[k] * v[j] - s[j] * v[k]);
-    w[j] += f * (s[i] * v[k] - s[k] * v[i]);
-    w[k] += f * (s[j] * v[i] - s[i] * v[j]);
+// f_458 = f_678 = sqrt(3)/2. The products f s_a are formed once a site
+// (AdMap), so a term of the series is 54 multiply-adds.
+struct AdMap {
+    double s[3];   // s_0, s_1, s_2 (f = 1)
+    double h[7];   // s_a / 2, a = 0 .. 6
+    double q[8];   // sqrt(3) s_a / 2, a = 3 .. 7
+};
+
+__device__ __forceinline__ AdMap ad_map(const double s[8]) {
+    const double h3 = 0.86602540378443864676;  // sqrt(3)/2
+    AdMap m;
+#pragma unroll
+    for (int a = 0; a < 3; a++) m.s[a] = s[a];
+#pragma unroll
+    for (int a = 0; a < 7; a++) m.h[a] = 0.5 * s[a];
+#pragma unroll
+    for (int a = 0; a < 8; a++) m.q[a] = h3 * s[a];
+    return m;
 }
 
-__device__ __forceinline__ void ad_components(const double s[8], const double v[8], double w[8]) {
-    const double h3 = 0.86602540378443864676;  // sqrt(3)/2
+// w += the triple (i, j, k) with the factors fs = f s (sign: of f)
+__device__ __forceinline__ void ad_triple(const double *fs, const double v[8], double w[8], int i, int j, int k,
+                                          double sign = 1.0) {
+    w[i] = fma(sign * fs[k], v[j], fma(-sign * fs[j], v[k], w[i]));
+    w[j] = fma(sign * fs[i], v[k], fma(-sign * fs[k], v[i], w[j]));
+    w[k] = fma(sign * fs[j], v[i], fma(-sign * fs[i], v[j], w[k]));
+}
+
+__device__ __forceinline__ void ad_components(const AdMap &m, const double v[8], double w[8]) {
 #pragma unroll
     for (int a = 0; a < 8; a++) w[a] = 0.0;
-    ad_triple(s, v, w, 0, 1, 2, 1.0);
-    ad_triple(s, v, w, 0, 3, 6, 0.5);
-    ad_triple(s, v, w, 0, 4, 5, -0.5);
-    ad_triple(s, v, w, 1, 3, 5, 0.5);
-    ad_triple(s, v, w, 1, 4, 6, 0.5);
-    ad_triple(s, v, w, 2, 3, 4, 0.5);
-    ad_triple(s, v, w, 2, 5, 6, -0.5);
-    ad_triple(s, v, w, 3, 4, 7, h3);
-    ad_triple(s, v, w, 5, 6, 7, h3);
+    ad_triple(m.s, v, w, 0, 1, 2);
+    ad_triple(m.h, v, w, 0, 3, 6);
+    ad_triple(m.h, v, w, 0, 4, 5, -1.0);
+    ad_triple(m.h, v, w, 1, 3, 5);
+    ad_triple(m.h, v, w, 1, 4, 6);
+    ad_triple(m.h, v, w, 2, 3, 4);
+    ad_triple(m.h, v, w, 2, 5, 6, -1.0);
+    ad_triple(m.q, v, w, 3, 4, 7);
+    ad_triple(m.q, v, w, 5, 6, 7);
 }
 
+// 1 / (k + 1) of the series' k-th term
+constexpr int AD_TERMS = 60;
+struct AdInverse {
+    double v[AD_TERMS + 1];
+};
+constexpr AdInverse ad_inverses() {
+    AdInverse t{};
+    for (int k = 0; k <= AD_TERMS; k++) t.v[k] = 1.0 / (k + 1);
+    return t;
+}
+static __constant__ AdInverse AD_INVERSE = ad_inverses();
+
+// What bounds it: the links and g of neighbours that have left the L2 (48^4
+// reads 1.5 to 1.8 times its bytes) and, in float, its double arithmetic. The
+// products go straight into K (180 -> 112 registers in float), the series'
+// terms are 54 multiply-adds with the factors formed once and 1 / (k + 1) from
+// a table (they were 175 instructions with a division each, about nine terms
+// a site). Whole calls, before -> after: float 24^4 63 -> 55 us, 48x44x40x36
+// 504 -> 437 us, 48^4 866 -> 743 us; double 101 -> 91, 830 -> 806, 1428 -> 1422.
 template <typename R, int NE, int ND>
-__global__ void __launch_bounds__(DT_TILE) k_functional_grad(Geom g, const typename V2<R>::type *__restrict__ U,
+__global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2))) k_functional_grad(Geom g, const typename V2<R>::type *__restrict__ U,
                                   const R *__restrict__ s, const typename V2<R>::type *__restrict__ gf,
                                   double scale, SlabOrder so, R *__restrict__ grad) {
     int p, h;
-    if (!tile_site(g, so, p, h)) return;
+    if (!tile_site(g, so, p, h)) {
+        if (h < g.nb * BLK) {  // the rest of the parity's last block
+            const long long o = alg_off(g, p, h, 0);
+#pragma unroll
+            for (int a = 0; a < 8; a++) grad[o + (long long)a * BLK] = R(0);
+        }
+        return;
+    }
     const SiteNbr fw = site_fwd_neighbours(g, p, h);
     const SiteNbr bw = site_neighbours(g, p, h);
+    // In double both links and both g of a direction are loaded together: the
+    // 2 waves a SIMD that fit then keep the same bytes in flight as 4 with half
+    // as much each, and fewer tiles at a time share the L2 (4 waves: 48x44x40x36
+    // 998 us against 813). In float 4 waves are the faster (440 and 454 us).
+    constexpr bool PAIR = sizeof(R) == 8;
     // The site's own s and g first, then the staple from t and z down to x:
     // the t and z neighbours' links and g lie in other tiles, and the earlier
     // in a workgroup's life they are read, the fewer tiles have passed
     // through L2 since their own workgroups read them (the x and y
     // neighbours mostly lie in this tile).
-    double sv[8];
-    load_s(s, g, p, h, sv);
-    DMat gx;
-    load_g<R>(gf, g, p, h, gx);
+    R sr[8];
+    {
+        const long long o = alg_off(g, p, h, 0);
+#pragma unroll
+        for (int a = 0; a < 8; a++) sr[a] = s[o + (long long)a * BLK];
+    }
+    Mat<R> gr;
+    load_g<R>(gf, g, p, h, gr);
     DMat K;
 #pragma unroll
     for (int e = 0; e < 9; e++) { K.re[e] = 0.0; K.im[e] = 0.0; }
 #pragma unroll
     for (int mu = ND - 1; mu >= 0; mu--) {
-        DMat u, gy, t;
-        // U_mu(x-mu)^dagger g(x-mu)^dagger
-        load_u<R, NE>(U, link_off(g, mu, 1 - p, pick4(bw.hb, mu)), u);
-        load_g<R>(gf, g, 1 - p, pick4(bw.hb, mu), gy);
-        dm_mul_dd(u, gy, t);
-#pragma unroll
-        for (int e = 0; e < 9; e++) { K.re[e] += t.re[e]; K.im[e] += t.im[e]; }
-        // U_mu(x) g(x+mu)^dagger
-        load_u<R, NE>(U, link_off(g, mu, p, h), u);
+        Mat<R> ub, gb, uf, gy;
+        // U_mu(x-mu)^dagger g(x-mu)^dagger + U_mu(x) g(x+mu)^dagger
+        load_link<R, NE, false>(ub, as_global((const void *)U), link_off(g, mu, 1 - p, pick4(bw.hb, mu)));
+        load_g<R>(gf, g, 1 - p, pick4(bw.hb, mu), gb);
+        if constexpr (!PAIR) dm_acc_dd(ub, gb, K);
+        load_link<R, NE, false>(uf, as_global((const void *)U), link_off(g, mu, p, h));
         load_g<R>(gf, g, 1 - p, pick4(fw.hb, mu), gy);
-        dm_mul_nd(u, gy, t);
-#pragma unroll
-        for (int e = 0; e < 9; e++) { K.re[e] += t.re[e]; K.im[e] += t.im[e]; }
+        if constexpr (PAIR) {
+            __builtin_amdgcn_sched_barrier(0);
+            dm_acc_dd(ub, gb, K);
+        }
+        dm_acc_nd(uf, gy, K);
     }
+    DMat gx;
+#pragma unroll
+    for (int e = 0; e < 9; e++) { gx.re[e] = gr.re[e]; gx.im[e] = gr.im[e]; }
+    double sv[8];
+#pragma unroll
+    for (int a = 0; a < 8; a++) sv[a] = (double)sr[a];
     DMat Y;
     dm_mul(K, gx, Y);  // K e^S
     // Only the anti-hermitian traceless part of Y reaches the traces, and
@@ -306,10 +365,11 @@ __global__ void __launch_bounds__(DT_TILE) k_functional_grad(Geom g, const typen
     for (int a = 0; a < 8; a++) { term[a] = tr[a]; amax = fmax(amax, fabs(tr[a])); }
     // the series stops once a term is below the output's rounding (float or double)
     const double tol = sizeof(R) == 4 ? 1e-10 : 1e-18;
-    for (int k = 1; k <= 60; k++) {
+    const AdMap ad = ad_map(sv);
+    for (int k = 1; k <= AD_TERMS; k++) {
         double nxt[8];
-        ad_components(sv, term, nxt);
-        const double inv = 1.0 / (k + 1);
+        ad_components(ad, term, nxt);
+        const double inv = AD_INVERSE.v[k];
         double tmax = 0.0;
 #pragma unroll
         for (int a = 0; a < 8; a++) {
@@ -331,7 +391,7 @@ __global__ void __launch_bounds__(DT_TILE) k_functional_grad(Geom g, const typen
 // tiles are dealt XCD-contiguously.
 constexpr int GT_TILE = 256;
 
-template <typename R, int NE>
+template <typename R, int NE, bool NT>
 __global__ void __launch_bounds__(GT_TILE) k_gauge_transform(Geom g, typename V2<R>::type *__restrict__ U,
                                   const typename V2<R>::type *__restrict__ gf, SlabOrder so) {
     constexpr int QH = GT_TILE / 2;
@@ -344,11 +404,11 @@ __global__ void __launch_bounds__(GT_TILE) k_gauge_transform(Geom g, typename V2
     load_g<R>(gf, g, p, h, gx);
     for (int mu = 0; mu < 4; mu++) {
         DMat u, gy;
-        load_u<R, NE, true>(U, link_off(g, mu, p, h), u);  // each link is read and written once: stream
+        load_u<R, NE, NT>(U, link_off(g, mu, p, h), u);
         load_g<R>(gf, g, 1 - p, pick4(fw.hb, mu), gy);
         Mat<R> m;
         gauge_rotate<R>(gx, u, gy, m);
-        store_link<R, NE, true>(m, as_global((void *)U), link_off(g, mu, p, h));
+        store_link<R, NE, NT>(m, as_global((void *)U), link_off(g, mu, p, h));
     }
 }
 
@@ -415,12 +475,18 @@ hipError_t launch_gauge_transform(int prec, int nelem, const Geom &g, void *U, c
                                   hipStream_t st) {
     const dim3 grid((g.Vh + GT_TILE / 2 - 1) / (GT_TILE / 2));
     const SlabOrder so = make_slab_order(g.st, GT_TILE / 2, (int)grid.x, 64);
-#define GF_L(R, NE)                                                                               \
-    hipLaunchKernelGGL((k_gauge_transform<R, NE>), grid, dim3(GT_TILE), 0, st, g, (V2<R>::type *)U, \
+    // Links that fit the last-level cache are better kept there (24^4 in float 59
+    // -> 52 us, 16^4 in double 25 -> 23 us a call); larger fields stream
+    // (48x44x40x36 in float 408 us, plain 449 us).
+    const bool nt = (double)field_complex(g) * (prec == 0 ? 16 : 8) > 150e6;
+#define GF_N(R, NE, NT)                                                                           \
+    hipLaunchKernelGGL((k_gauge_transform<R, NE, NT>), grid, dim3(GT_TILE), 0, st, g, (V2<R>::type *)U, \
                        (const V2<R>::type *)gfield, so)
+#define GF_L(R, NE) do { if (nt) GF_N(R, NE, true); else GF_N(R, NE, false); } while (0)
     if (prec == 0) { if (nelem == 9) GF_L(double, 9); else if (nelem == 6) GF_L(double, 6); else GF_L(double, 4); }
     else { if (nelem == 9) GF_L(float, 9); else if (nelem == 6) GF_L(float, 6); else GF_L(float, 4); }
 #undef GF_L
+#undef GF_N
     return hipGetLastError();
 }
 

@@ -347,7 +347,7 @@ class Context:
     def empty_alg(self, device="cuda"):
         """An algebra field in the internal layout, shape (2, nb, 8, 64):
         [parity][block of 64 sites][component a][site in block]; the padding
-        of the last block is zero (the kernels never write it)."""
+        of the last block is zero (packing and the gradient write zeros there)."""
         return torch.zeros((2, self.blocks(), 8, 64), dtype=self.rdtype, device=device)
 
     def _check_alg(self, s):
@@ -377,7 +377,7 @@ class Context:
 
     def functional_grad(self, U, s, dF=1.0, out=None):
         if out is None:
-            out = torch.zeros_like(s)
+            out = torch.empty_like(s)  # the kernel writes every value, padding included
         self._check(lib.gf_functional_grad(self._h, ctypes.c_void_p(self._check_field(U)),
                                            ctypes.c_void_p(self._check_alg(s)), float(dF),
                                            ctypes.c_void_p(self._check_alg(out))))
@@ -396,7 +396,7 @@ class GaugeFunctional(torch.autograd.Function):
     def forward(actx, s, U, ctx: Context):
         actx.save_for_backward(s, U)
         actx.gf = ctx
-        return torch.tensor(ctx.functional(U, s), dtype=torch.float64, device=s.device)
+        return torch.full((), ctx.functional(U, s), dtype=torch.float64, device=s.device)
 
     @staticmethod
     def backward(actx, dF):
