@@ -112,8 +112,7 @@ typedef struct gf_params {
                                (SU(4): >= 2) */
     int block_threads;      /* 0 = default, else 64, 128, 192 or 256 */
     int nontemporal;        /* 1 = streaming (non-temporal) link loads/stores,
-                               0 = plain, -1 = default for the lattice size
-                               (SU(2)/SU(4) kernels always stream) */
+                               0 = plain, -1 = default for the lattice size */
     int use_graph;          /* 1 = replay each check period as a hipGraph */
     int timing;             /* 1 = time every half-sweep with hipEvents */
     const char *log_path;   /* NULL = no log. Else the fix drivers (gf_fix,

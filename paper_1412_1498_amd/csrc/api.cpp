@@ -203,11 +203,19 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
     const bool f64 = prec == GF_F64, c8 = nc == 3 && nelem == 4;
     const double half = 0.5 * sites;
     if (nc != 3) {
-        // SU(4) links need two lanes a site (registers); double SU(2) is fastest with two
-        s.lps = (nc == 4 || f64) ? 2 : 1;
-        s.block = 128;
-        s.nt = 1;
-        s.order = 0;
+        // SU(4) links need two lanes a site (registers), four while that fills
+        // the chip better (8^4 in float 9.9 us with two, 8.2 us with four);
+        // SU(2) one, two on few sites and in double. The rest as for SU(3)
+        // below: SU(4) in float at 24^4 64 us plain in XCD shares, 75 us
+        // streaming; at 16^4 (34 MB) 16.0 and 14.5 us; at 32^4 189 us plain in
+        // dispatch order, 201 us streaming in shares.
+        if (nc == 4) s.lps = half * 4 <= 512 * 64 ? 4 : 2;
+        else s.lps = f64 || half * 2 <= 1024 * 64 ? 2 : 1;
+        s.block = bytes <= 230e6 ? 64 : 128;
+        // From about 1 GB on shares again (SU(4) in double 36^4 648 -> 616 us),
+        // from 2 GB on streaming (48^4 1964 -> 1837 us).
+        s.nt = (bytes > 16e6 && bytes < (nc == 4 ? 70e6 : 48e6)) || bytes > 2.2e9;
+        s.order = n == 1 && (bytes <= 230e6 || bytes > 1.2e9);
     } else if (bytes <= 230e6) {
         // Fields in the last-level cache. Few sites: more lanes a site shorten
         // a wave's work while the chip has idle SIMDs anyway (1024 of them);
@@ -953,7 +961,6 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
                     Schedule s{lps_list[li], block_list[bi], nt, order, 0};
                     s.lds = sweep_lds(s, ctx->nc, ctx->nelem, total_bytes());
                     if (ctx->nc == 4 && s.lps < 2) continue;       // registers
-                    if (ctx->nc != 3 && nt != 1) continue;         // SU(N) links are always non-temporal
                     ctx->sched = s;
                     if ((rc = build_tiles(ctx))) break;
                     for (int w = 0; w < 2 && rc == GF_OK; w++) rc = half_sweep(ctx, w & 1, 0, ctx->d_ones);

@@ -93,29 +93,30 @@ __device__ __forceinline__ void apply_right_dag_n(const MatN<R, N> &u, const Mat
         }
 }
 
-template <typename R, int N, int LPS, bool RU>
+template <typename R, int N, int LPS, bool NT, bool RU>
 __device__ __forceinline__ void or_site_n(const CfgDesc &d, int p, int h, int sub) {
     constexpr int L = 8 / LPS;  // links per lane
     constexpr int E = N * N;
     const Geom &g = d.g;
     gchar *U = as_global(d.U);
-    const SiteNbr nb = site_neighbours(g, p, h);
+    SiteNbr nb = site_neighbours(g, p, h);
     const bool landau = d.gauge == 0;
 
-    long long off[L];
     bool bwd[L], in[L];
 #pragma unroll
     for (int k = 0; k < L; k++) {
         const int slot = sub * L + k;
-        const int mu = slot >> 1;
-        const bool b = (slot & 1) != 0;
-        off[k] = b ? link_off(g, mu, 1 - p, pick4(nb.hb, mu)) : link_off(g, mu, p, h);
-        bwd[k] = b;
-        in[k] = landau || mu != 3;
+        bwd[k] = (slot & 1) != 0;  // compile-time unless LPS == 8
+        in[k] = landau || (slot >> 1) != 3;
     }
+    auto slot_off = [&](int k) {
+        const int mu = (sub * L + k) >> 1;
+        return bwd[k] ? link_off(g, mu, 1 - p, pick4(nb.hb, mu)) : link_off(g, mu, p, h);
+    };
     MatN<R, N> w[L];
 #pragma unroll
-    for (int k = 0; k < L; k++) load_link_n<R, N, true>(w[k], U, off[k]);
+    for (int k = 0; k < L; k++) load_link_n<R, N, NT>(w[k], U, slot_off(k));
+    __builtin_amdgcn_sched_barrier(0);  // all loads before the first use, as in the SU(3) sweep
 
     DMN<N> K;
 #pragma unroll
@@ -169,6 +170,10 @@ __device__ __forceinline__ void or_site_n(const CfgDesc &d, int p, int h, int su
 #pragma unroll
     for (int e = 0; e < E; e++) { G.re[e] = (R)T.re[e]; G.im[e] = (R)T.im[e]; }
 
+    // places recomputed, as in the SU(3) sweep
+    asm("" : "+v"(h));
+#pragma unroll
+    for (int mu = 0; mu < 4; mu++) asm("" : "+v"(nb.hb[mu]));
 #pragma unroll
     for (int k = 0; k < L; k++) {
         MatN<R, N> o;
@@ -187,33 +192,34 @@ __device__ __forceinline__ void or_site_n(const CfgDesc &d, int p, int h, int su
             apply_left_n(w[k], G, o);
         }
         if constexpr (RU) reunitarise_n(o);
-        store_link_n<R, N, true>(o, U, off[k]);
+        store_link_n<R, N, NT>(o, U, slot_off(k));
     }
 }
 
-template <typename R, int N, int LPS, bool RU>
+template <typename R, int N, int LPS, bool NT, bool RU>
 __global__ void __launch_bounds__(256)
 k_sun_half_sweep(const CfgDesc *__restrict__ desc, const int *__restrict__ tile_cfg,
                  const int *__restrict__ active, int parity, int order) {
-    const int tile = order ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int b = parity ? xcd_reverse(blockIdx.x, gridDim.x) : (int)blockIdx.x;  // as in the SU(3) sweep
+    const int tile = order ? xcd_tile(b, gridDim.x) : b;
     const int c = tile_cfg[tile];
     if (!active[c]) return;
     const CfgDesc d = desc[c];
     const int h = (tile - d.tile0) * (int)(blockDim.x / LPS) + (int)(threadIdx.x / LPS);
     if (h >= d.g.Vh) return;
-    or_site_n<R, N, LPS, RU>(d, parity, h, threadIdx.x % LPS);
+    or_site_n<R, N, LPS, NT, RU>(d, parity, h, threadIdx.x % LPS);
 }
 
 template <typename R, int N, int LPS>
 hipError_t launch_sun_t(const Schedule &s, const CfgDesc *d_desc, const int *d_tile_cfg,
                         const int *d_active, int ntiles, int parity, int reunit, hipStream_t st) {
     if (ntiles <= 0) return hipSuccess;
-    if (reunit)
-        hipLaunchKernelGGL((k_sun_half_sweep<R, N, LPS, true>), dim3(ntiles), dim3(s.block), 0, st,
-                           d_desc, d_tile_cfg, d_active, parity, s.order);
-    else
-        hipLaunchKernelGGL((k_sun_half_sweep<R, N, LPS, false>), dim3(ntiles), dim3(s.block), 0, st,
-                           d_desc, d_tile_cfg, d_active, parity, s.order);
+#define GF_S(NT, RU)                                                                                \
+    hipLaunchKernelGGL((k_sun_half_sweep<R, N, LPS, NT, RU>), dim3(ntiles), dim3(s.block), s.lds, st, \
+                       d_desc, d_tile_cfg, d_active, parity, s.order)
+    if (reunit) { if (s.nt) GF_S(true, true); else GF_S(false, true); }
+    else { if (s.nt) GF_S(true, false); else GF_S(false, false); }
+#undef GF_S
     return hipGetLastError();
 }
 

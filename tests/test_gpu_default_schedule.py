@@ -64,3 +64,19 @@ def test_ensemble_default_gives_the_members_own_bits(gf):
         Vs.append(U)
     ens.batch_fix(Us, 1.7, 0.0, 4)
     assert all(torch.equal(u, v) for u, v in zip(Us, Vs))
+
+
+@pytest.mark.parametrize("nc,dims", [(2, (2, 2, 2, 2)), (2, (10, 6, 4, 14)), (2, (16, 14, 18, 16)), (4, (2, 2, 2, 2)),
+                                     (4, (10, 6, 4, 14)), (4, (12, 12, 12, 12)), (4, (16, 14, 18, 16))])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_sun_default_schedule_gives_the_same_bits(gf, nc, dims, prec):
+    from paper_1412_1498_amd import synth
+    A = synth.random_sun_field(dims, nc, 0.4, 5).to("cuda", torch.complex128 if prec == 0 else torch.complex64)
+    out = []
+    for kw in ({}, dict(lanes_per_site=2, block_threads=128, nontemporal=1, tile_order=0),
+               dict(lanes_per_site=8, block_threads=64, nontemporal=0, tile_order=1)):
+        c = gf.Context(dims, prec=prec, nc=nc, params=gf.default_params(prec, reunit_every=2, **kw))
+        U = c.pack(A)
+        c.sweeps(U, 1.7, 3)
+        out.append(U)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
