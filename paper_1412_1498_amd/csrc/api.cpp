@@ -457,9 +457,17 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
         nq += d.nqtiles;
     }
     ctx->nqtiles = nq;
-    // an ensemble's tiles are several lattices end to end: plain order there
-    if (n == 1) {
-        const Geom &g0 = ctx->desc[0].g;
+    // Plain order for an ensemble, whose tiles are several lattices end to end, and
+    // for fields up to 100 MB: in plain order an XCD walks the tiles that the sweep
+    // before gave it, and finds in its L2 what slab blocks fetch from the last-level
+    // cache. A sweep and a check, slabs -> plain order: double 16^4 (38 MB) 50.9 ->
+    // 41.8 us, 20^4 (92 MB) 85.7 -> 84.7, float 20^4 (46 MB) 65 -> 58, 24^4 (96 MB)
+    // 91.2 -> 91.0, SU(2) 24^4 (42 MB) 57 -> 48, SU(4) 16^4 (34 MB) 56 -> 47. Beyond,
+    // nothing is left of it, and with the field out of the caches the slabs' fewer
+    // reads count: 28^4 double (354 MB) 309 and 314, float 32^4 (302 MB) 259 and 278.
+    const Geom &g0 = ctx->desc[0].g;
+    const double bytes0 = (double)field_complex(g0) * 2 * (prec == GF_F64 ? 8 : 4);
+    if (n == 1 && bytes0 > 100e6) {
         const int nd = ctx->desc[0].gauge == GF_LANDAU ? 4 : 3;
         const long long tile_bytes = (long long)QTILE * nd * ctx->nelem * 2 * (prec == GF_F64 ? 8 : 4);
         ctx->qslab = pick_slab_order(g0.st, g0.sz, g0.hx, g0.nz, QTILE / 2, nq, tile_bytes);
