@@ -151,8 +151,7 @@ __global__ void __launch_bounds__(256) k_expS(Geom g, const R *__restrict__ s, t
 
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double sh[16];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = v + __shfl_xor(v, m);
+    v = wave_sum(v);
     const int wid = threadIdx.x / 64, lane = threadIdx.x % 64;
     if (lane == 0) sh[wid] = v;
     __syncthreads();

@@ -24,12 +24,6 @@
 
 namespace gf {
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = v + __shfl_xor(v, m);
-    return v;
-}
-
 // Sum a pair over a workgroup of up to 1024 lanes (fixed order): result in
 // lane 0.
 __device__ __forceinline__ void block_sum2(double &a, double &b) {
@@ -224,6 +218,8 @@ k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ par
     const int c = blockIdx.x, n = gridDim.x;
     if (out.active && !out.active[c]) return;
     const CfgDesc d = desc[c];
+    // read ahead of the sum: behind its barrier each would be a trip to memory more
+    const int it0 = out.active ? out.iters[c] : 0, k0 = out.ring ? out.count[0] : 0;
     double fs, ts;
     sum_partials(partials + 2 * (size_t)d.qtile0, d.nqtiles, fs, ts);
     if (threadIdx.x == 0) {
@@ -235,19 +231,18 @@ k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ par
             out.result[2 * c + 1] = th;
             return;
         }
-        const int it = out.iters[c] + swept;
+        const int it = it0 + swept;
         const int on = !(th < eps) && isfinite(F) && isfinite(th);
         out.iters[c] = it;
         out.active[c] = on;
         if (out.ring) {
-            const int k = out.count[0];
-            CheckRec *r = out.ring + k % CHECK_RING;
+            CheckRec *r = out.ring + k0 % CHECK_RING;
             r->F = F;
             r->theta = th;
             r->active = on;
             r->iters = it;
-            __hip_atomic_store(&r->seq, k + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-            out.count[0] = k + 1;
+            __hip_atomic_store(&r->seq, k0 + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            out.count[0] = k0 + 1;
         } else {
             out.result[2 * c] = F;
             out.result[2 * c + 1] = th;

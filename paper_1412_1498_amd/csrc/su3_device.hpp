@@ -16,6 +16,64 @@ template <typename R> struct V2;
 template <> struct V2<float> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct V2<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
+// x of lane l gets lane l ^ M's value (both lanes active): M < 16 by DPP
+// moves within rows of 16 lanes (quad permutations, and for 4 the mirror
+// image of each half row, turned back quad by quad).
+template <int M>
+__device__ __forceinline__ int dpp_xor(int x) {
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8, "within a row");
+    if constexpr (M == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);       // quad_perm 1 0 3 2
+    else if constexpr (M == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
+    else if constexpr (M == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true); // row_ror 8
+    else  // i -> 7 - i -> i ^ 4
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+}
+
+// v of this lane plus v of lane ^ M, in registers: a shuffle through the LDS
+// crossbar is a trip to the one unit that all waves of the CU share, 72 of
+// them a site at four lanes. A sweep and a check with shuffles and without:
+// double 4^4 22.2 -> 20.5 us, 12^4 28.2 -> 26.4, float 16^4 32.3 -> 30.4,
+// SU(4) double 8^4 31.7 -> 28.7; nothing from 22x18x26x30 on, where memory
+// bounds.
+template <int M>
+__device__ __forceinline__ double xor_sum(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+    auto join = [](unsigned l, unsigned h) {
+        return __builtin_bit_cast(double, (unsigned long long)h << 32 | l);
+    };
+    if constexpr (M < 16) {
+        return v + join((unsigned)dpp_xor<M>((int)lo), (unsigned)dpp_xor<M>((int)hi));
+    } else {
+        // both halves (or row pairs) of v side by side: the sum of the two is
+        // v + v(lane ^ M) in either order
+        const auto l = M == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                               : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = M == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                               : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return join(l[0], h[0]) + join(l[1], h[1]);
+    }
+}
+
+// Sum over a wave by the fixed butterfly 32, 16, .., 1 (every lane gets it).
+__device__ __forceinline__ double wave_sum(double v) {
+    v = xor_sum<32>(v);
+    v = xor_sum<16>(v);
+    v = xor_sum<8>(v);
+    v = xor_sum<4>(v);
+    v = xor_sum<2>(v);
+    return xor_sum<1>(v);
+}
+
+// Sum over the LPS neighbouring lanes of a site, by 1, 2, 4.
+template <int LPS>
+__device__ __forceinline__ double site_sum(double v) {
+    if constexpr (LPS >= 2) v = xor_sum<1>(v);
+    if constexpr (LPS >= 4) v = xor_sum<2>(v);
+    if constexpr (LPS >= 8) v = xor_sum<4>(v);
+    return v;
+}
+
 // Global-address-space views: a uniform (scalar) base pointer plus a 32-bit
 // per-lane byte offset lets the compiler emit global_load/store with an SGPR
 // base instead of 64-bit flat addresses per lane.

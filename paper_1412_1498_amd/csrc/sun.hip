@@ -6,7 +6,7 @@
 // eight links; K(x) = sum_mu [U_mu(x) + U_mu(x - mu)^dagger] (eq. 5) is
 // built once in double over the link slots (fwd 0, bwd 0, ..., fwd 3,
 // bwd 3) in the fixed tree ((s0 + s1) + (s2 + s3)) + ((s4 + s5) + (s6 + s7)),
-// the upper levels by xor-shuffles between the LPS lanes of a site; every
+// the upper levels across the LPS lanes of a site; every
 // subgroup step (eq. 6 on the (a, b) block, exact principal power for the
 // over-relaxation) acts on K (K <- G K) and on the running product T, and
 // the eight links are rotated once by T (rounded to the link precision).
@@ -139,13 +139,8 @@ __device__ __forceinline__ void or_site_n(const CfgDesc &d, int p, int h, int su
                     tr[k] = tr[k] + tr[k + step];
                     ti[k] = ti[k] + ti[k + step];
                 }
-#pragma unroll
-            for (int m = 1; m < LPS; m <<= 1) {
-                tr[0] = tr[0] + __shfl_xor(tr[0], m);
-                ti[0] = ti[0] + __shfl_xor(ti[0], m);
-            }
-            K.re[e] = tr[0];
-            K.im[e] = ti[0];
+            K.re[e] = site_sum<LPS>(tr[0]);
+            K.im[e] = site_sum<LPS>(ti[0]);
         }
     }
 

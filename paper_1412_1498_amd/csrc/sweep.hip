@@ -31,7 +31,7 @@
 // 8/LPS links. Link slots are ordered (fwd 0, bwd 0, fwd 1, bwd 1, ...,
 // fwd 3, bwd 3); a lane owns consecutive slots and K is summed over slots in
 // the fixed tree ((s0 + s1) + (s2 + s3)) + ((s4 + s5) + (s6 + s7)), the
-// upper levels by xor-shuffles between the site's lanes. Every lane then
+// upper levels across the site's lanes. Every lane then
 // runs the (cheap, double) subgroup steps redundantly. The tree does not
 // depend on LPS, so all schedules give bitwise identical links.
 #include "su3_device.hpp"
@@ -166,7 +166,7 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
 
     // K = sum over slots of U (forward) or U^dagger (backward), promoted to
     // double; per element, the lane's slots are summed in place in the fixed
-    // tree, then the site's lanes combine by xor-shuffles.
+    // tree, then the site's lanes combine.
     DM K;
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -188,13 +188,8 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
                     tr[k] = tr[k] + tr[k + step];
                     ti[k] = ti[k] + ti[k + step];
                 }
-#pragma unroll
-            for (int m = 1; m < LPS; m <<= 1) {
-                tr[0] = tr[0] + __shfl_xor(tr[0], m);
-                ti[0] = ti[0] + __shfl_xor(ti[0], m);
-            }
-            K.re[e] = tr[0];
-            K.im[e] = ti[0];
+            K.re[e] = site_sum<LPS>(tr[0]);
+            K.im[e] = site_sum<LPS>(ti[0]);
         }
     }
 
