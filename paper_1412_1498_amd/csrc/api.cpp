@@ -56,11 +56,11 @@ struct gf_ctx {
     int *d_active = nullptr;         // per member (fix drivers)
     int *d_ones = nullptr;           // per member, all 1 (plain calls)
     int *d_iters = nullptr;
-    int *d_count = nullptr;          // checks published to the ring
+    unsigned *d_count = nullptr;     // checks published to the ring
     double *h_result = nullptr;      // pinned, written by the kernels: 2n results
     int *h_flags = nullptr;          // pinned: n active, n iters (written by the kernels), n ones, n zeros, 1 count
     CheckRec *ring = nullptr;        // pinned, written by the kernels: last checks of a single lattice
-    int checks = 0;                  // checks taken from the ring
+    unsigned checks = 0;             // number of the last check taken from the ring
     Schedule sched{};
     long long sweeps_done = 0;
     std::string err;
@@ -383,12 +383,32 @@ int quality_launch(gf_ctx *ctx, const int *d_active, int update, int swept, doub
     return GF_OK;
 }
 
-// Wait for check number `seq` of a single lattice: its record's number is
-// written last. The stream is asked now and then, so that a failed launch
-// ends the wait.
-int wait_check(gf_ctx *ctx, int seq, CheckRec *out) {
-    const CheckRec *r = ctx->ring + (seq - 1) % CHECK_RING;
-    for (long long spin = 0; __atomic_load_n(&r->seq, __ATOMIC_ACQUIRE) != seq; spin++) {
+struct Check {
+    double F, theta;
+    int active, iters;
+};
+
+// Check number `seq` of a single lattice, if all words of its record are there.
+bool read_check(const gf_ctx *ctx, unsigned seq, Check *out) {
+    const CheckRec &r = ctx->ring[(seq - 1) % CHECK_RING];
+    unsigned v[6];
+    for (int i = 0; i < 6; i++) {
+        const unsigned long long w = __atomic_load_n(&r.w[i], __ATOMIC_RELAXED);
+        if ((unsigned)(w >> 32) != seq) return false;
+        v[i] = (unsigned)w;
+    }
+    const unsigned long long f = (unsigned long long)v[1] << 32 | v[0], t = (unsigned long long)v[3] << 32 | v[2];
+    std::memcpy(&out->F, &f, sizeof f);
+    std::memcpy(&out->theta, &t, sizeof t);
+    out->active = (int)v[4];
+    out->iters = (int)v[5];
+    return true;
+}
+
+// Wait for check number `seq`. The stream is asked now and then, so that a
+// failed launch ends the wait.
+int wait_check(gf_ctx *ctx, unsigned seq, Check *out) {
+    for (long long spin = 0; !read_check(ctx, seq, out); spin++) {
         if (spin % 1024 != 1023) continue;
         const hipError_t e = hipStreamQuery(ctx->stream);
         if (e == hipErrorNotReady) {
@@ -396,9 +416,9 @@ int wait_check(gf_ctx *ctx, int seq, CheckRec *out) {
             continue;
         }
         HIPTRY(ctx, e);
-        CHECK(ctx, __atomic_load_n(&r->seq, __ATOMIC_ACQUIRE) == seq, GF_EDEVICE, "a check's result is missing");
+        CHECK(ctx, read_check(ctx, seq, out), GF_EDEVICE, "a check's result is missing");
+        break;
     }
-    *out = *r;
     return GF_OK;
 }
 
@@ -741,7 +761,8 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
     // every member starts active with zero sweeps
     HIPTRY(ctx, hipMemcpyAsync(ctx->d_active, ctx->h_flags + 2 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
     HIPTRY(ctx, hipMemcpyAsync(ctx->d_iters, ctx->h_flags + 3 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
-    ctx->h_flags[4 * n] = ctx->checks;
+    ctx->checks += CHECK_RING;  // past any record that a call before left behind when it failed
+    ctx->h_flags[4 * n] = (int)ctx->checks;
     HIPTRY(ctx, hipMemcpyAsync(ctx->d_count, ctx->h_flags + 4 * n, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
     if ((rc = quality_launch(ctx, ctx->d_active, 1, 0, eps, ctx->stream))) return rc;
     // members active before a check (those whose result it refreshed)
@@ -802,7 +823,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         const bool ahead = !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
         const long long sweeps0 = ctx->sweeps_done;
         int enqueued = 0, pending = 1;
-        CheckRec k{};
+        Check k{};
         for (;;) {
             while (pending < (ahead ? 2 : 1) && enqueued < max_iter) {
                 const int m = std::min(ctx->p.check_every, max_iter - enqueued);

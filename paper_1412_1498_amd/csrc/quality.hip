@@ -216,10 +216,13 @@ __global__ void __launch_bounds__(QFINAL)
 k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ partials, QualityOut out, int swept,
                 double eps, double ncol) {
     const int c = blockIdx.x, n = gridDim.x;
-    if (out.active && !out.active[c]) return;
+    // everything is read ahead of the first use of any: one trip to memory, not one after the other
+    const int active = out.active ? out.active[c] : 1;
+    const int it0 = out.active ? out.iters[c] : 0;
+    const unsigned k0 = out.ring ? out.count[0] : 0;
     const CfgDesc d = desc[c];
-    // read ahead of the sum: behind its barrier each would be a trip to memory more
-    const int it0 = out.active ? out.iters[c] : 0, k0 = out.ring ? out.count[0] : 0;
+    __builtin_amdgcn_sched_barrier(0);
+    if (!active) return;
     double fs, ts;
     sum_partials(partials + 2 * (size_t)d.qtile0, d.nqtiles, fs, ts);
     if (threadIdx.x == 0) {
@@ -236,13 +239,16 @@ k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ par
         out.iters[c] = it;
         out.active[c] = on;
         if (out.ring) {
-            CheckRec *r = out.ring + k0 % CHECK_RING;
-            r->F = F;
-            r->theta = th;
-            r->active = on;
-            r->iters = it;
-            __hip_atomic_store(&r->seq, k0 + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-            out.count[0] = k0 + 1;
+            unsigned long long *w = out.ring[k0 % CHECK_RING].w;
+            const unsigned long long f = __builtin_bit_cast(unsigned long long, F);
+            const unsigned long long t = __builtin_bit_cast(unsigned long long, th);
+            const unsigned v[6] = {(unsigned)f, (unsigned)(f >> 32), (unsigned)t, (unsigned)(t >> 32), (unsigned)on,
+                                   (unsigned)it};
+#pragma unroll
+            for (int i = 0; i < 6; i++)
+                __hip_atomic_store(w + i, (unsigned long long)(k0 + 1u) << 32 | v[i], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+            out.count[0] = k0 + 1u;
         } else {
             out.result[2 * c] = F;
             out.result[2 * c + 1] = th;

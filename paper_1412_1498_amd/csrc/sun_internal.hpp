@@ -20,11 +20,14 @@ hipError_t launch_sun_quality(int prec, int nc, const CfgDesc *d_desc, const int
 // Where the final reduction leaves its results. All but iters, active and
 // count are pinned host memory, written by the kernel itself: reading a check
 // back then takes no copies, only the wait for it.
-struct CheckRec {       // one finished check of a single lattice's fix driver
-    double F, theta;
-    int active, iters;
-    int seq;            // number of the check, written last
-    int pad;
+// One finished check of a single lattice's fix driver: the halves of F and
+// theta, active and iters, each in a 64-bit store of its own with the check's
+// number in the upper half. The record is there once all six numbers are; no
+// store waits for another to reach host memory, as a flag written last would.
+// With the member's entry and counters read together at the start, a sweep and a
+// check in double at 12^4 26.4 -> 25.6 us, in float at 16^4 30.4 -> 29.8.
+struct CheckRec {
+    unsigned long long w[6], pad[2];
 };
 constexpr int CHECK_RING = 8;
 
@@ -34,7 +37,7 @@ struct QualityOut {
     int *iters;         // device: per member, sweeps so far
     int *flags;         // pinned copies of active (n) and iters (n)
     CheckRec *ring;     // null, or CHECK_RING records: check k goes to record (k - 1) mod CHECK_RING
-    int *count;         // device: checks published so far
+    unsigned *count;    // device: checks published so far
 };
 
 // F and theta of every member from its partials, normalised for nc colours.
