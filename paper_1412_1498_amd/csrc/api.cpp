@@ -77,6 +77,7 @@ struct gf_ctx {
     // components of Delta, and the tables of roots of unity for the x, y, z
     // and t lengths (FFT_MAX_N complex doubles each), then their 4 sin^2(pi m / L)
     void *d_spec = nullptr;
+    double *d_sdpart = nullptr;      // F and theta's partials of the Delta pass
     void *d_roots = nullptr;
     // per-time-slice quality: partials and results
     double *d_slice_part = nullptr;
@@ -378,7 +379,7 @@ int quality_launch(gf_ctx *ctx, const int *d_active, int update, int swept, doub
                                        ctx->nqtiles, ctx->d_partials, ctx->qslab, st));
     // pinned memory has one address on host and device
     const QualityOut out{ctx->h_result, update ? ctx->d_active : nullptr, ctx->d_iters, ctx->h_flags,
-                         ctx->n == 1 ? ctx->ring : nullptr, ctx->d_count};
+                         update && ctx->n == 1 ? ctx->ring : nullptr, ctx->d_count};
     HIPTRY(ctx, launch_quality_final(ctx->nc, ctx->d_desc, ctx->n, ctx->d_partials, out, swept, eps, st));
     return GF_OK;
 }
@@ -403,6 +404,16 @@ bool read_check(const gf_ctx *ctx, unsigned seq, Check *out) {
     out->active = (int)v[4];
     out->iters = (int)v[5];
     return true;
+}
+
+// The checks of a driver call are numbered past any record that a call before
+// left behind when it failed.
+int start_checks(gf_ctx *ctx) {
+    int *count = ctx->h_flags + 4 * ctx->n;
+    ctx->checks += CHECK_RING;
+    *count = (int)ctx->checks;
+    HIPTRY(ctx, hipMemcpyAsync(ctx->d_count, count, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    return GF_OK;
 }
 
 // Wait for check number `seq`. The stream is asked now and then, so that a
@@ -586,6 +597,7 @@ int gf_destroy(gf_ctx *ctx) {
     (void)hipFree(ctx->d_iters);
     (void)hipFree(ctx->d_count);
     (void)hipFree(ctx->d_spec);
+    (void)hipFree(ctx->d_sdpart);
     (void)hipFree(ctx->d_roots);
     (void)hipFree(ctx->d_gfield);
     (void)hipFree(ctx->d_fpart);
@@ -761,9 +773,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
     // every member starts active with zero sweeps
     HIPTRY(ctx, hipMemcpyAsync(ctx->d_active, ctx->h_flags + 2 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
     HIPTRY(ctx, hipMemcpyAsync(ctx->d_iters, ctx->h_flags + 3 * n, n * sizeof(int), hipMemcpyHostToDevice, ctx->stream));
-    ctx->checks += CHECK_RING;  // past any record that a call before left behind when it failed
-    ctx->h_flags[4 * n] = (int)ctx->checks;
-    HIPTRY(ctx, hipMemcpyAsync(ctx->d_count, ctx->h_flags + 4 * n, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
+    if ((rc = start_checks(ctx))) return rc;
     if ((rc = quality_launch(ctx, ctx->d_active, 1, 0, eps, ctx->stream))) return rc;
     // members active before a check (those whose result it refreshed)
     std::vector<int> was_active(n, 1);
@@ -1131,6 +1141,11 @@ int sd_prepare(gf_ctx *ctx) {
         ctx->d_spec = nullptr;
         return fail(ctx, GF_ENOMEM, "cannot allocate the Fourier acceleration buffers");
     }
+    if (!ctx->d_sdpart &&
+        hipMalloc(&ctx->d_sdpart, 2 * (size_t)sd_delta_groups(make_fft_site(g)) * sizeof(double)) != hipSuccess) {
+        ctx->d_sdpart = nullptr;
+        return fail(ctx, GF_ENOMEM, "cannot allocate the Fourier acceleration buffers");
+    }
     if (!ctx->d_roots) {
         void *w = nullptr;
         if (hipMalloc(&w, 4 * (size_t)FFT_MAX_N * (16 + 8)) != hipSuccess)
@@ -1160,7 +1175,10 @@ const double *sd_p2(const gf_ctx *ctx) { return (const double *)sd_roots(ctx, 4)
 // Delta is formed in the forward x pass and g in the inverse one; the filter
 // sits in the last forward pass (t for Landau, z for Coulomb), between its
 // forward and inverse transform.
-int sd_step_impl(gf_ctx *ctx, void *U, double alpha) {
+// Everything of a step that only reads the links: Delta, the filter, the g
+// field. With `check`, F and theta of those links come from the Delta pass and
+// are published as the next check.
+int sd_direction(gf_ctx *ctx, const void *U, double alpha, bool check) {
     const Geom &g = ctx->desc[0].g;
     const int gauge = ctx->desc[0].gauge;
     const bool landau = gauge == GF_LANDAU;
@@ -1178,15 +1196,28 @@ int sd_step_impl(gf_ctx *ctx, void *U, double alpha) {
     const void *wx = sd_roots(ctx, 0), *wy = sd_roots(ctx, 1), *wz = sd_roots(ctx, 2);
     const double *p2 = sd_p2(ctx);
     void *spec = ctx->d_spec;
-    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, gauge, g, fx, wx, U, spec, st));
+    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, gauge, g, fx, wx, U, spec, check ? ctx->d_sdpart : nullptr, st));
+    if (check) {
+        const QualityOut out{nullptr, nullptr, nullptr, nullptr, ctx->ring, ctx->d_count};
+        HIPTRY(ctx, launch_quality_final(3, ctx->d_desc, 1, ctx->d_sdpart, out, 0, 0.0, st, sd_delta_groups(fx)));
+    }
     HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, ly, wy, p2, spec, 1, -1, 0, st));
     if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, lz, wz, p2, spec, 2, -1, 0, st));
     HIPTRY(ctx, launch_fft_axis(ctx->prec, flt, llt, sd_roots(ctx, last), p2, spec, last, -1, 1, st));
     if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, lz, wz, p2, spec, 2, 1, 0, st));
     HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, ly, wy, p2, spec, 1, 1, 0, st));
     HIPTRY(ctx, launch_sd_fx_gfield(ctx->prec, g, fx, wx, ctx->d_spec, ctx->d_gfield, st));
-    HIPTRY(ctx, launch_gauge_transform(ctx->prec, ctx->nelem, g, U, ctx->d_gfield, st));
     return GF_OK;
+}
+
+int sd_apply(gf_ctx *ctx, void *U) {
+    HIPTRY(ctx, launch_gauge_transform(ctx->prec, ctx->nelem, ctx->desc[0].g, U, ctx->d_gfield, ctx->stream));
+    return GF_OK;
+}
+
+int sd_step_impl(gf_ctx *ctx, void *U, double alpha) {
+    const int rc = sd_direction(ctx, U, alpha, false);
+    return rc ? rc : sd_apply(ctx, U);
 }
 
 int check_alpha(gf_ctx *ctx, double alpha) {
@@ -1223,19 +1254,32 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
     log_open(ctx);
     ctx->log_calls++;
     *iters = 0;
-    if ((rc = gf_quality(ctx, U, F, theta))) return rc;
-    log_check(ctx, true, 0, 0, *F, *theta, t0);
-    log_flush(ctx);
+    if ((rc = start_checks(ctx))) return rc;
     int it = 0;
-    while (it < max_iter && !(*theta < eps)) {
+    for (;;) {
+        // A check that a step can follow comes from that step's own Delta pass, with
+        // the step's direction enqueued behind it (it leaves the links alone): a pass
+        // over the links and the wait for the result less. F and theta as returned are
+        // those of gf_quality, which the last check is.
+        bool last = it >= max_iter;
+        if (!last) {
+            Check k{};
+            if ((rc = sd_direction(ctx, U, alpha, true)) || (rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
+            ctx->checks++;
+            *F = k.F;
+            *theta = k.theta;
+            last = k.theta < eps || !std::isfinite(k.F) || !std::isfinite(k.theta);
+        }
+        if (last && (rc = gf_quality(ctx, U, F, theta))) return rc;
+        log_check(ctx, true, 0, it, *F, *theta, t0);
+        log_flush(ctx);
+        if (it >= max_iter || *theta < eps) break;
         const int m = std::min(ctx->p.check_every, max_iter - it);
-        for (int k = 0; k < m; k++)
+        if ((rc = sd_apply(ctx, U))) return rc;
+        for (int k = 1; k < m; k++)
             if ((rc = sd_step_impl(ctx, U, alpha))) return rc;
         it += m;
         *iters = it;
-        if ((rc = gf_quality(ctx, U, F, theta))) return rc;
-        log_check(ctx, true, 0, it, *F, *theta, t0);
-        log_flush(ctx);
     }
     return *theta < eps ? GF_OK : GF_NOT_CONVERGED;
 }

@@ -426,8 +426,9 @@ namespace {
 // double, A = M - M^dagger, whose traceless part is Delta (the trace part
 // drops out of these traces, so only Im of the diagonal and the off-diagonal
 // entries of A enter).
-template <typename R, int NE>
-__device__ __forceinline__ void delta_components(const Geom &g, int nd, const gchar *U, int p, int h, double o[8]) {
+template <typename R, int NE, bool SUMS>
+__device__ __forceinline__ void delta_components(const Geom &g, int nd, const gchar *U, int p, int h, double o[8],
+                                                 double &fsum, double &tsum) {
     const SiteNbr nb = site_neighbours(g, p, h);
     double mr[9], mi[9];
 #pragma unroll
@@ -441,6 +442,7 @@ __device__ __forceinline__ void delta_components(const Geom &g, int nd, const gc
             mr[e] += (double)b.re[e] - (double)f.re[e];
             mi[e] += (double)b.im[e] - (double)f.im[e];
         }
+        if (SUMS) fsum += (double)f.re[0] + (double)f.re[4] + (double)f.re[8];
     }
     double ar[9], ai[9];
 #pragma unroll
@@ -459,6 +461,14 @@ __device__ __forceinline__ void delta_components(const Geom &g, int nd, const gc
     o[5] = 0.5 * (ai[7] + ai[5]);
     o[6] = 0.5 * (ar[5] - ar[7]);
     o[7] = 0.5 * r3 * (ai[0] + ai[4] - 2.0 * ai[8]);
+    if (SUMS) {
+        const double trr = (ar[0] + ar[4] + ar[8]) / 3.0;
+        const double tri = (ai[0] + ai[4] + ai[8]) / 3.0;
+#pragma unroll
+        for (int r = 0; r < 3; r++) { ar[4 * r] -= trr; ai[4 * r] -= tri; }
+#pragma unroll
+        for (int e = 0; e < 9; e++) tsum += ar[e] * ar[e] + ai[e] * ai[e];
+    }
 }
 
 // g = reunit(1 + i H), H = sum_a s_a lambda_a (the first-order exponential
@@ -519,10 +529,17 @@ __device__ __forceinline__ long long spec_index(const Geom &g, int nkx, const Ro
 // row holds both parities, so a site's x-backward link is the other
 // parity's forward link of the same tile and its y-backward link that of the
 // previous row.
-template <typename R, int NE>
+//
+// SUMS: the workgroup's sums for F and theta as well (of site rows instead of
+// F/theta's tiles), one pair per workgroup into part: a step that follows a
+// check has every link in registers here, so the check needs no pass of its own.
+// Steps with a check each, before and after: double 20x28x18x30 (Coulomb) 1059
+// -> 915 us for five, 32^4 3670 -> 3155, float 16^4 735 -> 596 for ten; float 48^4
+// with one check in five 8150 -> 7840.
+template <typename R, int NE, bool SUMS>
 __global__ void __launch_bounds__(FFT_BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 k_sd_delta_fx(Geom g, int nd, const typename V2<R>::type *__restrict__ Uv, FftSite f, const Cd *__restrict__ Wg,
-              typename V2<R>::type *__restrict__ spec, SlabOrder so) {
+              typename V2<R>::type *__restrict__ spec, SlabOrder so, double *__restrict__ part) {
     extern __shared__ Cd lds[];
     const int nx = g.nx, nc = 4 * f.ys;
     const Tile t = tile_setup(lds, Wg, nx, nc + 1, f.dnc);
@@ -531,20 +548,34 @@ k_sd_delta_fx(Geom g, int nd, const typename V2<R>::type *__restrict__ Uv, FftSi
     // slab order over tiles of ys site rows: a time slice is ny nz rows, so
     // the rows holding the t-backward links were read ny nz / ys tiles
     // before, in the same column block
-    const long long sr0 = (long long)slab_tile(xcd_tile(blockIdx.x, gridDim.x), so) * f.ys;
+    const int tile = slab_tile(xcd_tile(blockIdx.x, gridDim.x), so);
+    const long long sr0 = (long long)tile * f.ys;
     row_info(ri, g, sr0, f.ys, f.srows);
     __syncthreads();
     const gchar *U = as_global((const void *)Uv);
+    double fsum = 0.0, tsum = 0.0;
     for (int idx = threadIdx.x; idx < f.ys * nx; idx += blockDim.x) {
         const int yl = (int)fdiv((unsigned)idx, f.dn), x = idx - yl * nx;
         const RowInfo r = ri[yl];
         double o[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (r.zy >= 0) {
             const int lx = x + nx * (int)(sr0 + yl);  // x + nx (y + ny (z + nz t))
-            delta_components<R, NE>(g, nd, U, (x + r.y + r.z + r.t) & 1, lx >> 1, o);
+            delta_components<R, NE, SUMS>(g, nd, U, (x + r.y + r.z + r.t) & 1, lx >> 1, o, fsum, tsum);
         }
 #pragma unroll
         for (int c = 0; c < 4; c++) t.a[x * t.ld + yl * 4 + c] = Cd{o[2 * c], o[2 * c + 1]};
+    }
+    if constexpr (SUMS) {
+        __shared__ double sums[FFT_BLOCK / 64][2];
+        fsum = wave_sum(fsum);
+        tsum = wave_sum(tsum);
+        if (threadIdx.x % 64 == 0) { sums[threadIdx.x / 64][0] = fsum; sums[threadIdx.x / 64][1] = tsum; }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double v = 0.0;
+            for (int w = 0; w < FFT_BLOCK / 64; w++) v += sums[w][threadIdx.x];
+            part[2 * tile + threadIdx.x] = v;
+        }
     }
     if (f.n1) lds_split_forward(t, f.n1, f.n2, nc);
     else lds_dft<-1>(t, f.pl, nx, nc);
@@ -951,19 +982,23 @@ static size_t site_lds_bytes(const FftSite &f) {
     return lds_bytes(f.n, 4 * f.ys + 1) + (size_t)f.ys * sizeof(RowInfo);
 }
 
+int sd_delta_groups(const FftSite &f) { return (int)((f.srows + f.ys - 1) / f.ys); }
+
 hipError_t launch_sd_delta_fx(int prec, int nelem, int gauge, const Geom &g, const FftSite &f, const void *W,
-                              const void *U, void *spec, hipStream_t st) {
-    const dim3 grid((unsigned)((f.srows + f.ys - 1) / f.ys));
+                              const void *U, void *spec, double *part, hipStream_t st) {
+    const dim3 grid((unsigned)sd_delta_groups(f));
     const size_t sh = site_lds_bytes(f);
     const int nd = gauge == 0 ? 4 : 3;
     const Cd *w = (const Cd *)W;
     const SlabOrder so = make_slab_order(g.ny * g.nz, f.ys, (int)grid.x);
-#define GF_L(R, NE)                                                                                   \
-    hipLaunchKernelGGL((k_sd_delta_fx<R, NE>), grid, dim3(FFT_BLOCK), sh, st, g, nd,                 \
-                       (const V2<R>::type *)U, f, w, (V2<R>::type *)spec, so)
+#define GF_S(R, NE, SUMS)                                                                             \
+    hipLaunchKernelGGL((k_sd_delta_fx<R, NE, SUMS>), grid, dim3(FFT_BLOCK), sh, st, g, nd,           \
+                       (const V2<R>::type *)U, f, w, (V2<R>::type *)spec, so, part)
+#define GF_L(R, NE) do { if (part) GF_S(R, NE, true); else GF_S(R, NE, false); } while (0)
     if (prec == 0) { if (nelem == 9) GF_L(double, 9); else if (nelem == 6) GF_L(double, 6); else GF_L(double, 4); }
     else { if (nelem == 9) GF_L(float, 9); else if (nelem == 6) GF_L(float, 6); else GF_L(float, 4); }
 #undef GF_L
+#undef GF_S
     return hipGetLastError();
 }
 

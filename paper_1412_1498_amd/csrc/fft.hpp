@@ -104,9 +104,11 @@ FftLine make_fft_line(const Geom &g, int axis);
 // W: a table of exp(2 pi i m / n), m < n, for the transform's length; p2: one
 // of 4 sin^2(pi m / n) (launch_fft_roots fills both)
 hipError_t launch_fft_roots(void *W, double *p2, int n, hipStream_t st);
-// Delta (eq. 3) of every site -> its components' x-transformed half spectrum
+// Delta (eq. 3) of every site -> its components' x-transformed half spectrum;
+// with part, also sd_delta_groups(f) pairs of partial sums for F and theta
+int sd_delta_groups(const FftSite &f);
 hipError_t launch_sd_delta_fx(int prec, int nelem, int gauge, const Geom &g, const FftSite &f, const void *W,
-                              const void *U, void *spec, hipStream_t st);
+                              const void *U, void *spec, double *part, hipStream_t st);
 // half spectrum -> inverse x transform -> g = reunit(1 + X) as the g field (gfield_off)
 hipError_t launch_sd_fx_gfield(int prec, const Geom &g, const FftSite &f, const void *W, const void *spec,
                                void *gfield, hipStream_t st);

@@ -214,7 +214,7 @@ __device__ __forceinline__ void sum_partials(const double *__restrict__ partials
 // result and publish nothing.
 __global__ void __launch_bounds__(QFINAL)
 k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ partials, QualityOut out, int swept,
-                double eps, double ncol) {
+                double eps, double ncol, int npart) {
     const int c = blockIdx.x, n = gridDim.x;
     // everything is read ahead of the first use of any: one trip to memory, not one after the other
     const int active = out.active ? out.active[c] : 1;
@@ -224,20 +224,23 @@ k_quality_final(const CfgDesc *__restrict__ desc, const double *__restrict__ par
     __builtin_amdgcn_sched_barrier(0);
     if (!active) return;
     double fs, ts;
-    sum_partials(partials + 2 * (size_t)d.qtile0, d.nqtiles, fs, ts);
+    if (npart > 0) sum_partials(partials, npart, fs, ts);
+    else sum_partials(partials + 2 * (size_t)d.qtile0, d.nqtiles, fs, ts);
     if (threadIdx.x == 0) {
         const int nd = d.gauge == 0 ? 4 : 3;
         const double F = fs / (nd * ncol * (double)d.g.V);
         const double th = ts / (ncol * (double)d.g.V);
-        if (!out.active) {
+        if (!out.active && !out.ring) {
             out.result[2 * c] = F;
             out.result[2 * c + 1] = th;
             return;
         }
         const int it = it0 + swept;
         const int on = !(th < eps) && isfinite(F) && isfinite(th);
-        out.iters[c] = it;
-        out.active[c] = on;
+        if (out.active) {
+            out.iters[c] = it;
+            out.active[c] = on;
+        }
         if (out.ring) {
             unsigned long long *w = out.ring[k0 % CHECK_RING].w;
             const unsigned long long f = __builtin_bit_cast(unsigned long long, F);
@@ -425,9 +428,9 @@ hipError_t launch_quality_tstream(int prec, int nelem, const Geom &g, const CfgD
 }
 
 hipError_t launch_quality_final(int nc, const CfgDesc *d_desc, int n, const double *d_partials,
-                                const QualityOut &out, int swept, double eps, hipStream_t st) {
+                                const QualityOut &out, int swept, double eps, hipStream_t st, int npart) {
     hipLaunchKernelGGL(k_quality_final, dim3(n), dim3(QFINAL), 0, st, d_desc, d_partials, out, swept, eps,
-                       (double)nc);
+                       (double)nc, npart);
     return hipGetLastError();
 }
 

@@ -33,15 +33,16 @@ constexpr int CHECK_RING = 8;
 
 struct QualityOut {
     double *result;     // 2 per member: F, theta
-    int *active;        // device: per member, 1 until theta < eps or not finite (null: plain evaluation)
+    int *active;        // device: per member, 1 until theta < eps or not finite (null: all)
     int *iters;         // device: per member, sweeps so far
     int *flags;         // pinned copies of active (n) and iters (n)
     CheckRec *ring;     // null, or CHECK_RING records: check k goes to record (k - 1) mod CHECK_RING
     unsigned *count;    // device: checks published so far
 };
 
-// F and theta of every member from its partials, normalised for nc colours.
+// F and theta of every member from its partials, normalised for nc colours;
+// with npart > 0, of the one member from its npart pairs at d_partials.
 hipError_t launch_quality_final(int nc, const CfgDesc *d_desc, int n, const double *d_partials,
-                                const QualityOut &out, int swept, double eps, hipStream_t st);
+                                const QualityOut &out, int swept, double eps, hipStream_t st, int npart = 0);
 
 }  // namespace gf
