@@ -566,15 +566,17 @@ k_sd_delta_fx(Geom g, int nd, const typename V2<R>::type *__restrict__ Uv, FftSi
         for (int c = 0; c < 4; c++) t.a[x * t.ld + yl * 4 + c] = Cd{o[2 * c], o[2 * c + 1]};
     }
     if constexpr (SUMS) {
-        __shared__ double sums[FFT_BLOCK / 64][2];
+        __shared__ Cd sums[FFT_BLOCK / 64];
         fsum = wave_sum(fsum);
         tsum = wave_sum(tsum);
-        if (threadIdx.x % 64 == 0) { sums[threadIdx.x / 64][0] = fsum; sums[threadIdx.x / 64][1] = tsum; }
+        if (threadIdx.x % 64 == 0) sums[threadIdx.x / 64] = Cd{fsum, tsum};
         __syncthreads();
-        if (threadIdx.x < 2) {
-            double v = 0.0;
-            for (int w = 0; w < FFT_BLOCK / 64; w++) v += sums[w][threadIdx.x];
-            part[2 * tile + threadIdx.x] = v;
+        if (threadIdx.x == 0) {
+            Cd v = sums[0];
+#pragma unroll
+            for (int w = 1; w < FFT_BLOCK / 64; w++) { v.x += sums[w].x; v.y += sums[w].y; }
+            part[2 * tile] = v.x;
+            part[2 * tile + 1] = v.y;
         }
     }
     if (f.n1) lds_split_forward(t, f.n1, f.n2, nc);
