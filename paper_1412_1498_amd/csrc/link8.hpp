@@ -102,36 +102,80 @@ GF_HD void link8_phase_decode(R p, R *c, R *s) {
     *c = zero ? R(0) : (neg ? -ac : ac);
 }
 
+// Where the n2 = 0 case is dealt with. In double by selects in place. In float
+// (link8_late) at the end, behind a branch of the whole wave (link8_any; on the
+// host, of the one link): what it takes, two elements more of the rotated link,
+// a phase and the selects, is a tenth of the instructions of the sweep, which
+// they bound. With the same bits, a sweep and a tenth of a check in float:
+// 40x40x40x24 181 -> 174 us, 48^4 560 -> 534, 32^4 127 -> 121. In double a
+// one-lane site has no registers left for the branches.
+template <typename R> constexpr bool link8_late = sizeof(R) == 4;
+
+GF_HD bool link8_any(bool deg) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ballot_w64(deg) != 0;
+#else
+    return deg;
+#endif
+}
+
 // The four stored complex values of a 3x3 link (re[9], im[9], element (r, c)
 // at 3r + c): U01, U02, U10, (phase code of U00, phase code of U20).
 // When U01 = U02 = 0, the third value is U11 and the second phase code is
-// that of U12 instead (see above).
+// that of U12 instead (see above); the two are used, and by the compiler
+// formed, only behind that branch.
 template <typename R>
 GF_HD void link8_compress(const R *re, const R *im, R *sre, R *sim) {
     const bool deg = re[1] == R(0) && im[1] == R(0) && re[2] == R(0) && im[2] == R(0);
+    R vr = re[3], vi = im[3];
+    if constexpr (link8_late<R>) {
+        R wr = re[6], wi = im[6];
+        if (link8_any(deg)) {
+            vr = deg ? re[4] : vr; vi = deg ? im[4] : vi;
+            wr = deg ? re[5] : wr; wi = deg ? im[5] : wi;
+        }
+        sre[3] = link8_phase_code<R>(re[0], im[0]);
+        sim[3] = link8_phase_code<R>(wr, wi);
+    } else {
+        vr = deg ? re[4] : vr; vi = deg ? im[4] : vi;
+        sre[3] = link8_phase_code<R>(re[0], im[0]);
+        sim[3] = deg ? link8_phase_code<R>(re[5], im[5]) : link8_phase_code<R>(re[6], im[6]);
+    }
     sre[0] = re[1]; sim[0] = im[1];
     sre[1] = re[2]; sim[1] = im[2];
-    sre[2] = deg ? re[4] : re[3]; sim[2] = deg ? im[4] : im[3];
-    sre[3] = link8_phase_code<R>(re[0], im[0]);
-    sim[3] = deg ? link8_phase_code<R>(re[5], im[5]) : link8_phase_code<R>(re[6], im[6]);
+    sre[2] = vr; sim[2] = vi;
+}
+
+// c2 = -conj(a1 b3 - a3 b1), c3 = conj(a1 b2 - a2 b1) from rows 0 and 1
+template <typename R>
+GF_HD void link8_row2(R *re, R *im) {
+    const R a1r = re[0], a1i = im[0], a2r = re[1], a2i = im[1], a3r = re[2], a3i = im[2];
+    const R b1r = re[3], b1i = im[3], b2r = re[4], b2i = im[4], b3r = re[5], b3i = im[5];
+    const R x2r = link8_dot<R>(a1r, b3r, -a1i, b3i) - link8_dot<R>(a3r, b1r, -a3i, b1i);
+    const R x2i = link8_dot<R>(a1r, b3i, a1i, b3r) - link8_dot<R>(a3r, b1i, a3i, b1r);
+    const R x3r = link8_dot<R>(a1r, b2r, -a1i, b2i) - link8_dot<R>(a2r, b1r, -a2i, b1i);
+    const R x3i = link8_dot<R>(a1r, b2i, a1i, b2r) - link8_dot<R>(a2r, b1i, a2i, b1r);
+    re[7] = -x2r; im[7] = x2i;
+    re[8] = x3r; im[8] = -x3i;
 }
 
 template <typename R>
 GF_HD void link8_reconstruct(const R *sre, const R *sim, R *re, R *im) {
     const R a2r = sre[0], a2i = sim[0], a3r = sre[1], a3i = sim[1];
     const R n2 = link8_dot<R>(a2r, a2r, a2i, a2i) + link8_dot<R>(a3r, a3r, a3i, a3i);
-    const bool deg = !(n2 > R(0));        // U01 = U02 = 0: the slot holds U11
+    const bool deg = !(n2 > R(0));         // U01 = U02 = 0: the slot holds U11
+    const bool now = !link8_late<R> && deg;
     const R sl = link8_dot<R>(sre[2], sre[2], sim[2], sim[2]);
-    const R b1r = deg ? R(0) : sre[2], b1i = deg ? R(0) : sim[2];
+    const R b1r = now ? R(0) : sre[2], b1i = now ? R(0) : sim[2];
     R s, c;
     link8_phase_decode<R>(sre[3], &c, &s);
     const R m1 = link8_sqrt<R>(fmax(R(1) - n2, R(0)));
     const R a1r = m1 * c, a1i = m1 * s;
     link8_phase_decode<R>(sim[3], &c, &s);
     // |U20| in general; |U12| = sqrt(1 - |U11|^2) in the n2 = 0 case
-    const R m3 = link8_sqrt<R>(fmax((deg ? R(1) : n2) - sl, R(0)));
+    const R m3 = link8_sqrt<R>(fmax((now ? R(1) : n2) - sl, R(0)));
     const R zr = m3 * c, zi = m3 * s;
-    const R c1r = deg ? R(0) : zr, c1i = deg ? R(0) : zi;
+    const R c1r = now ? R(0) : zr, c1i = now ? R(0) : zi;
     // conj(a1) a2 b1, conj(a1) a3 b1
     const R pr = link8_dot<R>(a1r, a2r, a1i, a2i), pi = link8_dot<R>(a1r, a2i, -a1i, a2r);   // conj(a1) a2
     const R qr = link8_dot<R>(a1r, a3r, a1i, a3i), qi = link8_dot<R>(a1r, a3i, -a1i, a3r);   // conj(a1) a3
@@ -140,24 +184,23 @@ GF_HD void link8_reconstruct(const R *sre, const R *sim, R *re, R *im) {
     // conj(a3) conj(c1) = conj(a3 c1), conj(a2) conj(c1) = conj(a2 c1)
     const R u3r = link8_dot<R>(a3r, c1r, -a3i, c1i), u3i = -link8_dot<R>(a3r, c1i, a3i, c1r);
     const R u2r = link8_dot<R>(a2r, c1r, -a2i, c1i), u2i = -link8_dot<R>(a2r, c1i, a2i, c1r);
-    const R inv = link8_rcp<R>(deg ? R(1) : n2);
-    // n2 = 0: U11 from the slot, U12 from its phase code and modulus
-    const R b2r = deg ? sre[2] : -(t1r + u3r) * inv, b2i = deg ? sim[2] : -(t1i + u3i) * inv;
-    const R b3r = deg ? zr : (u2r - t2r) * inv, b3i = deg ? zi : (u2i - t2i) * inv;
-    // c2 = -conj(a1 b3 - a3 b1), c3 = conj(a1 b2 - a2 b1)
-    const R x2r = link8_dot<R>(a1r, b3r, -a1i, b3i) - link8_dot<R>(a3r, b1r, -a3i, b1i);
-    const R x2i = link8_dot<R>(a1r, b3i, a1i, b3r) - link8_dot<R>(a3r, b1i, a3i, b1r);
-    const R x3r = link8_dot<R>(a1r, b2r, -a1i, b2i) - link8_dot<R>(a2r, b1r, -a2i, b1i);
-    const R x3i = link8_dot<R>(a1r, b2i, a1i, b2r) - link8_dot<R>(a2r, b1i, a2i, b1r);
+    const R inv = link8_rcp<R>(now ? R(1) : n2);
     re[0] = a1r; im[0] = a1i;
     re[1] = a2r; im[1] = a2i;
     re[2] = a3r; im[2] = a3i;
     re[3] = b1r; im[3] = b1i;
-    re[4] = b2r; im[4] = b2i;
-    re[5] = b3r; im[5] = b3i;
+    // n2 = 0: U11 from the slot, U12 from its phase code and modulus
+    re[4] = now ? sre[2] : -(t1r + u3r) * inv; im[4] = now ? sim[2] : -(t1i + u3i) * inv;
+    re[5] = now ? zr : (u2r - t2r) * inv; im[5] = now ? zi : (u2i - t2i) * inv;
     re[6] = c1r; im[6] = c1i;
-    re[7] = -x2r; im[7] = x2i;
-    re[8] = x3r; im[8] = -x3i;
+    if (link8_late<R> && link8_any(deg)) {
+        const R m = link8_sqrt<R>(fmax(R(1) - sl, R(0)));
+        re[3] = deg ? R(0) : re[3]; im[3] = deg ? R(0) : im[3];
+        re[4] = deg ? sre[2] : re[4]; im[4] = deg ? sim[2] : im[4];
+        re[5] = deg ? m * c : re[5]; im[5] = deg ? m * s : im[5];
+        re[6] = deg ? R(0) : re[6]; im[6] = deg ? R(0) : im[6];
+    }
+    link8_row2<R>(re, im);
 }
 
 #undef GF_HD
