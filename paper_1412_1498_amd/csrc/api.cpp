@@ -213,10 +213,11 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
         if (nc == 4) s.lps = half * 4 <= 512 * 64 ? 4 : 2;
         else s.lps = f64 || half * 2 <= 1024 * 64 ? 2 : 1;
         s.block = bytes <= 230e6 ? 64 : 128;
-        // From about 1 GB on shares again (SU(4) in double 36^4 648 -> 616 us),
-        // from 2 GB on streaming (48^4 1964 -> 1837 us).
+        // SU(4) from about 1 GB on shares again (in double 36^4 648 -> 616 us; SU(2)
+        // in double 48^4 475 us in dispatch order, 499 in shares), both from 2 GB on
+        // streaming (SU(4) 48^4 1964 -> 1837 us).
         s.nt = (bytes > 16e6 && bytes < (nc == 4 ? 70e6 : 48e6)) || bytes > 2.2e9;
-        s.order = n == 1 && (bytes <= 230e6 || bytes > 1.2e9);
+        s.order = n == 1 && (bytes <= 230e6 || (nc == 4 && bytes > 1.2e9));
     } else if (bytes <= 230e6) {
         // Fields in the last-level cache. Few sites: more lanes a site shorten
         // a wave's work while the chip has idle SIMDs anyway (1024 of them);
