@@ -244,13 +244,18 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
         s.order = 0;
     } else {
         // plain access keeps the end of one half-sweep in the last-level cache
-        // for the start of the next; of 3 GB (double 48^4) that is too little
-        // to pay (1121 us streaming, 1128 us plain)
-        const bool huge = bytes > 2.2e9;
-        s.lps = f64 || huge ? 2 : 1;
-        s.block = 128;
-        s.nt = huge;
-        s.order = huge && n == 1;
+        // for the start of the next; of 3 GB in double (48^4) that is too little
+        // to pay (1121 us streaming, 1128 us plain). In float it pays up to some
+        // 4 GB: 48^3 x 96 (3.1 GB) 1112 us plain, one lane, 1165 us streaming in
+        // shares with two; 64^4 (4.8 GB) 1710 us streaming, two lanes in
+        // 256-thread workgroups, 1750 us in 128-thread ones. An ensemble as large
+        // (48^3 x 96 and 64 small lattices, 5.4 GB) 2106 us plain, 2215 streaming; in
+        // double (9 GB) 3360 us with one lane, 3389 with two.
+        const bool huge = bytes > (f64 ? 2.2e9 : 4e9);
+        s.lps = f64 ? (huge && n > 1 ? 1 : 2) : huge ? 2 : 1;
+        s.block = huge && !f64 && n == 1 ? 256 : 128;
+        s.nt = huge && (f64 || n == 1);
+        s.order = huge && f64 && n == 1;
     }
     if (p.lanes_per_site > 0) s.lps = p.lanes_per_site;
     if (p.block_threads > 0) s.block = p.block_threads;
