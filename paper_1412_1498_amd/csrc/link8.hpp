@@ -56,8 +56,9 @@ namespace gf {
 // made the float 8-real sweep instruction-bound. In double they are gf_rcp
 // and gf_sqrt, which round like the general operations but skip their range
 // scaling: a site's 8 links take 40 reciprocals and 32 square roots, half of
-// the double sweep's instructions in their general form. Float host code
-// uses the general operations.
+// the double sweep's instructions in their general form. gf_sqrt takes every
+// finite x >= 0, subnormal ones too (squares of elements below 1e-154). Float
+// host code uses the general operations.
 template <typename R> GF_HD R link8_rcp(R x) {
     if constexpr (sizeof(R) == 8) return gf_rcp(x);
 #if defined(__HIP_DEVICE_COMPILE__)
