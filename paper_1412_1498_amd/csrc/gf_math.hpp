@@ -155,10 +155,16 @@ GF_HD void gf_su2_overrelax(const double b[4], double omega, double r[4]) {
     const double v2 = fma(b[1], b[1], fma(b[2], b[2], b[3] * b[3]));
     const bool deg = !(v2 > 0.0);
     const double rv = deg ? 0.0 : gf_rsqrt(v2);  // 1 / |b_vec|
-    const double phi = gf_atan2_upper(T, v2 * rv, b[0]);
+    // |b_vec| and s / |b_vec| each by the product with rv and one correction: the
+    // products alone round once more than a root and a quotient do (near the
+    // solution 6.5e-17 instead of 5.3e-17 rms at omega 1.7)
+    double vn = v2 * rv;
+    vn = fma(fma(-vn, vn, v2), 0.5 * rv, vn);
+    const double phi = gf_atan2_upper(T, vn, b[0]);
     double s, c;
     gf_sincos(T, omega * phi, &s, &c);
-    const double f = -(s * rv);
+    double f = s * rv;
+    f = -fma(fma(-vn, f, s), rv, f);
     r[0] = c;
     r[1] = b[1] * f;
     r[2] = b[2] * f;
