@@ -287,15 +287,30 @@ static __constant__ AdInverse AD_INVERSE = ad_inverses();
 
 // What bounds it: the links and g of neighbours that have left the L2 (48^4
 // reads 1.5 to 1.8 times its bytes) and, in float, its double arithmetic. The
-// products go straight into K (180 -> 112 registers in float), the series'
+// products go straight into K (180 -> 128 registers in float), the series'
 // terms are 54 multiply-adds with the factors formed once and 1 / (k + 1) from
 // a table (they were 175 instructions with a division each, about nine terms
-// a site). Whole calls, before -> after: float 24^4 63 -> 55 us, 48x44x40x36
-// 504 -> 437 us, 48^4 866 -> 743 us; double 101 -> 91, 830 -> 806, 1428 -> 1422.
+// a site). Whole calls in Landau gauge, k_expS included, before -> after: float
+// 24^4 83 -> 72 us, 48x44x40x36 576 -> 487, 48^4 962 -> 815; double 116 -> 108,
+// 878 -> 822, 1500 -> 1415; 8-real links in float 102 -> 75, 709 -> 472,
+// 1180 -> 803, in double 168 -> 96, 1335 -> 752, 2250 -> 1283.
+//
+// Waves per SIMD asked for, per form, so that none spills: with four in every
+// float form 8-real links spilled 197 registers (48x44x40x36 1389 us). Their
+// directions stay a loop as well: unrolled, the decoding of all eight links is
+// spread over one another (324 registers, 635 us; 160 and 472 as a loop). Full
+// and 12-real links in float reach four waves without being asked to but in
+// one form.
 template <typename R, int NE, int ND>
-__global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2))) k_functional_grad(Geom g, const typename V2<R>::type *__restrict__ U,
-                                  const R *__restrict__ s, const typename V2<R>::type *__restrict__ gf,
-                                  double scale, SlabOrder so, R *__restrict__ grad) {
+constexpr int grad_waves() {
+    if (sizeof(R) == 8) return 2;
+    return NE == 4 ? 3 : NE == 9 && ND == 4 ? 4 : 2;
+}
+
+template <typename R, int NE, int ND>
+__global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(grad_waves<R, NE, ND>())))
+k_functional_grad(Geom g, const typename V2<R>::type *__restrict__ U, const R *__restrict__ s,
+                  const typename V2<R>::type *__restrict__ gf, double scale, SlabOrder so, R *__restrict__ grad) {
     int p, h;
     if (!tile_site(g, so, p, h)) {
         if (h < g.nb * BLK) {  // the rest of the parity's last block
@@ -307,11 +322,15 @@ __global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(si
     }
     const SiteNbr fw = site_fwd_neighbours(g, p, h);
     const SiteNbr bw = site_neighbours(g, p, h);
-    // In double both links and both g of a direction are loaded together: the
-    // 2 waves a SIMD that fit then keep the same bytes in flight as 4 with half
-    // as much each, and fewer tiles at a time share the L2 (4 waves: 48x44x40x36
-    // 998 us against 813). In float 4 waves are the faster (440 and 454 us).
-    constexpr bool PAIR = sizeof(R) == 8;
+    // In double both links and both g of a direction are loaded together, and no
+    // load of the next one before they are used: the 2 waves a SIMD that fit
+    // then keep the same bytes in flight as 4 with half as much each, and fewer
+    // tiles at a time share the L2 (4 waves: 48x44x40x36 998 us against 842).
+    // Not full links in four directions, where the larger footprint of a tile's
+    // loads costs more than it gives (48x44x40x36 842 us, one after the other 822;
+    // 48^4 1462 and 1415; in three directions 669 and 687, 1142 and 1165; 12-real
+    // 24^4 91 and 96). In float 4 waves are the faster (440 and 454 us).
+    constexpr bool PAIR = sizeof(R) == 8 && !(NE == 9 && ND == 4);
     // The site's own s and g first, then the staple from t and z down to x:
     // the t and z neighbours' links and g lie in other tiles, and the earlier
     // in a workgroup's life they are read, the fewer tiles have passed
@@ -328,7 +347,7 @@ __global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(si
     DMat K;
 #pragma unroll
     for (int e = 0; e < 9; e++) { K.re[e] = 0.0; K.im[e] = 0.0; }
-#pragma unroll
+#pragma clang loop unroll_count(sizeof(R) == 4 && NE == 4 ? 1 : ND)
     for (int mu = ND - 1; mu >= 0; mu--) {
         Mat<R> ub, gb, uf, gy;
         // U_mu(x-mu)^dagger g(x-mu)^dagger + U_mu(x) g(x+mu)^dagger
@@ -342,6 +361,7 @@ __global__ void __launch_bounds__(DT_TILE) __attribute__((amdgpu_waves_per_eu(si
             dm_acc_dd(ub, gb, K);
         }
         dm_acc_nd(uf, gy, K);
+        if constexpr (PAIR) __builtin_amdgcn_sched_barrier(0);
     }
     DMat gx;
 #pragma unroll
