@@ -314,7 +314,11 @@ int gf_gauge_transform(gf_ctx *ctx, void *U, const void *s);
 int gf_sd_step(gf_ctx *ctx, void *U, double alpha);
 
 /* Alg. 2: F, theta; while theta >= eps and fewer than max_iter steps: steps,
- * with F, theta every check_every steps. Returns GF_OK / GF_NOT_CONVERGED. */
+ * with F, theta every check_every steps. The F and theta returned, and the
+ * theta < eps that ends the run, are gf_quality's; the checks in between come
+ * from the next step's own pass over the links, which adds the same terms in
+ * another order, so their F and theta in the log can differ from gf_quality's
+ * in the last bits. Returns GF_OK / GF_NOT_CONVERGED. */
 int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int *iters, double *F,
               double *theta);
 

@@ -1266,7 +1266,10 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
         // A check that a step can follow comes from that step's own Delta pass, with
         // the step's direction enqueued behind it (it leaves the links alone): a pass
         // over the links and the wait for the result less. F and theta as returned are
-        // those of gf_quality, which the last check is.
+        // those of gf_quality, which the last check is. It also decides where the run
+        // ends: the Delta pass adds the same terms in another order, so that its theta is
+        // within 1e-12 of gf_quality's (some hundred roundings of 1.1e-16 on the largest
+        // lattices); from there down gf_quality is asked.
         bool last = it >= max_iter;
         if (!last) {
             Check k{};
@@ -1274,7 +1277,7 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
             ctx->checks++;
             *F = k.F;
             *theta = k.theta;
-            last = k.theta < eps || !std::isfinite(k.F) || !std::isfinite(k.theta);
+            last = k.theta < eps * (1.0 + 1e-12) || !std::isfinite(k.F) || !std::isfinite(k.theta);
         }
         if (last && (rc = gf_quality(ctx, U, F, theta))) return rc;
         log_check(ctx, true, 0, it, *F, *theta, t0);
