@@ -1181,13 +1181,25 @@ const double *sd_p2(const gf_ctx *ctx) { return (const double *)sd_roots(ctx, 4)
 // Delta is formed in the forward x pass and g in the inverse one; the filter
 // sits in the last forward pass (t for Landau, z for Coulomb), between its
 // forward and inverse transform.
-// Everything of a step that only reads the links: Delta, the filter, the g
-// field. With `check`, F and theta of those links come from the Delta pass and
-// are published as the next check.
-int sd_direction(gf_ctx *ctx, const void *U, double alpha, bool check) {
+// Everything of a step that only reads the links, in two parts: Delta with the
+// forward x transform, and the rest up to the g field. With `check`, F and theta
+// of those links come from the Delta pass and are published as the next check.
+int sd_delta(gf_ctx *ctx, const void *U, bool check) {
     const Geom &g = ctx->desc[0].g;
-    const int gauge = ctx->desc[0].gauge;
-    const bool landau = gauge == GF_LANDAU;
+    const FftSite fx = make_fft_site(g);
+    hipStream_t st = ctx->stream;
+    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, ctx->desc[0].gauge, g, fx, sd_roots(ctx, 0), U, ctx->d_spec,
+                                   check ? ctx->d_sdpart : nullptr, st));
+    if (check) {
+        const QualityOut out{nullptr, nullptr, nullptr, nullptr, ctx->ring, ctx->d_count};
+        HIPTRY(ctx, launch_quality_final(3, ctx->d_desc, 1, ctx->d_sdpart, out, 0, 0.0, st, sd_delta_groups(fx)));
+    }
+    return GF_OK;
+}
+
+int sd_gfield(gf_ctx *ctx, double alpha) {
+    const Geom &g = ctx->desc[0].g;
+    const bool landau = ctx->desc[0].gauge == GF_LANDAU;
     const FftSite fx = make_fft_site(g);
     const FftAxis fy = make_fft_axis(g, 1, !landau);
     const FftAxis fz = make_fft_axis(g, 2, !landau);
@@ -1202,11 +1214,6 @@ int sd_direction(gf_ctx *ctx, const void *U, double alpha, bool check) {
     const void *wx = sd_roots(ctx, 0), *wy = sd_roots(ctx, 1), *wz = sd_roots(ctx, 2);
     const double *p2 = sd_p2(ctx);
     void *spec = ctx->d_spec;
-    HIPTRY(ctx, launch_sd_delta_fx(ctx->prec, ctx->nelem, gauge, g, fx, wx, U, spec, check ? ctx->d_sdpart : nullptr, st));
-    if (check) {
-        const QualityOut out{nullptr, nullptr, nullptr, nullptr, ctx->ring, ctx->d_count};
-        HIPTRY(ctx, launch_quality_final(3, ctx->d_desc, 1, ctx->d_sdpart, out, 0, 0.0, st, sd_delta_groups(fx)));
-    }
     HIPTRY(ctx, launch_fft_axis(ctx->prec, fy, ly, wy, p2, spec, 1, -1, 0, st));
     if (landau) HIPTRY(ctx, launch_fft_axis(ctx->prec, fz, lz, wz, p2, spec, 2, -1, 0, st));
     HIPTRY(ctx, launch_fft_axis(ctx->prec, flt, llt, sd_roots(ctx, last), p2, spec, last, -1, 1, st));
@@ -1222,8 +1229,9 @@ int sd_apply(gf_ctx *ctx, void *U) {
 }
 
 int sd_step_impl(gf_ctx *ctx, void *U, double alpha) {
-    const int rc = sd_direction(ctx, U, alpha, false);
-    return rc ? rc : sd_apply(ctx, U);
+    int rc;
+    if ((rc = sd_delta(ctx, U, false)) || (rc = sd_gfield(ctx, alpha))) return rc;
+    return sd_apply(ctx, U);
 }
 
 int check_alpha(gf_ctx *ctx, double alpha) {
@@ -1270,10 +1278,18 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
         // ends: the Delta pass adds the same terms in another order, so that its theta is
         // within 1e-12 of gf_quality's (some hundred roundings of 1.1e-16 on the largest
         // lattices); from there down gf_quality is asked.
+        // A field that is fixed already takes no direction: on large lattices the first
+        // check is waited for before the transforms are enqueued (48^4 in float 1242 ->
+        // 763 us a call, 32^4 305 -> 176; a run that goes on loses 8 us once: 48^4, five
+        // steps 7842 -> 7850). On small ones that gap is worth more (4^4 in double, five
+        // steps 235 -> 275 us; a fixed field 75 -> 60).
+        const bool first = it == 0 && ctx->desc[0].g.V >= 1000000;
         bool last = it >= max_iter;
         if (!last) {
             Check k{};
-            if ((rc = sd_direction(ctx, U, alpha, true)) || (rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
+            if ((rc = sd_delta(ctx, U, true))) return rc;
+            if (!first && (rc = sd_gfield(ctx, alpha))) return rc;
+            if ((rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
             ctx->checks++;
             *F = k.F;
             *theta = k.theta;
@@ -1284,6 +1300,7 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
         log_flush(ctx);
         if (it >= max_iter || *theta < eps) break;
         const int m = std::min(ctx->p.check_every, max_iter - it);
+        if (first && (rc = sd_gfield(ctx, alpha))) return rc;
         if ((rc = sd_apply(ctx, U))) return rc;
         for (int k = 1; k < m; k++)
             if ((rc = sd_step_impl(ctx, U, alpha))) return rc;
