@@ -833,23 +833,38 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         // The host stays one period ahead of the check it waits for: a check
         // that ends the run retires the lattice on the device, and the period
         // already enqueued finds it retired and does nothing. Only for short
-        // periods, whose launches and read-back the GPU would wait for (4^4
-        // with a check every sweep: 38 us a sweep without and 23 us with, the copies saved included);
-        // a long one's launches hide behind the period itself.
-        const bool ahead = !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
+        // periods, whose launches and read-back the GPU would wait for (4^4 in
+        // double, 20 sweeps with a check each: 660 us without and 440 with); a
+        // long one's launches hide behind the period itself. And not where the
+        // next check will likely end the run, since launches that find the lattice
+        // retired still take 3 us each: theta is taken to fall as it did in the
+        // period before. With less than two checks to go by, five sweeps are the
+        // most to be thrown away (a field fixed already, 4^4, check every 5, 16 and
+        // 150 sweeps: 45, 45 and 45 us without, 68, 124 and 794 with; one period
+        // of a run 108, 214 and 1561 without, 88, 195 and 1499 with).
+        const bool brief = !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
+        double before = 0.0;  // theta of the check before the last
+        int taken = 0;
         const long long sweeps0 = ctx->sweeps_done;
         int enqueued = 0, pending = 1;
         Check k{};
+        auto ahead = [&]() {
+            if (!brief || eps == 0.0) return brief;  // no theta is below 0: max_iter sweeps
+            if (taken < 2) return ctx->p.check_every <= 5;
+            return k.theta * (k.theta / before) >= eps;
+        };
         for (;;) {
-            while (pending < (ahead ? 2 : 1) && enqueued < max_iter) {
+            while (pending < (ahead() ? 2 : 1) && enqueued < max_iter) {
                 const int m = std::min(ctx->p.check_every, max_iter - enqueued);
                 if ((rc = period(m))) return rc;
                 enqueued += m;
                 pending++;
             }
             if (pending == 0) break;
+            before = k.theta;
             if ((rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
             ctx->checks++;
+            taken++;
             pending--;
             ctx->h_result[0] = k.F;
             ctx->h_result[1] = k.theta;
