@@ -250,8 +250,11 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
 int gf_batch_quality(gf_ctx *ctx, void *const *U, double *F, double *theta);
 
 /* Time the candidate schedules (lanes per site, workgroup size,
- * non-temporal access, and for a single lattice the tile order) on a scratch copy of the members' fields U[i] and
- * keep the fastest in ctx. Every schedule gives bitwise the same links. If
+ * non-temporal access, and for a single lattice the tile order) on a scratch
+ * copy of the members' fields U[i] and keep the fastest in ctx; an ensemble is
+ * timed with every member active and with its largest alone, and keeps its
+ * schedule unless another is clearly faster over both. Every schedule gives
+ * bitwise the same links. If
  * cache_path is not NULL, a previous result for the same device, library
  * sources, colour number, precision, storage and lattice list is reused and
  * new results are appended. The context itself (single lattice or
