@@ -426,9 +426,23 @@ int start_checks(gf_ctx *ctx) {
     return GF_OK;
 }
 
-// Wait for check number `seq`. The stream is asked now and then, so that a
-// failed launch ends the wait.
-int wait_check(gf_ctx *ctx, unsigned seq, Check *out) {
+// Whether the process waits for its device by spinning (the runtime's default as
+// well) or has asked for waits that leave the core to others.
+bool waits_spin() {
+    unsigned flags = 0;
+    return hipGetDeviceFlags(&flags) != hipSuccess ||
+           !(flags & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync));
+}
+
+// Wait for check number `seq`: by the runtime's own wait for the stream, or (watch)
+// by watching its record, with the stream asked now and then, so that a failed
+// launch ends the wait.
+int wait_check(gf_ctx *ctx, unsigned seq, Check *out, bool watch) {
+    if (!watch) {
+        HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
+        CHECK(ctx, read_check(ctx, seq, out), GF_EDEVICE, "a check's result is missing");
+        return GF_OK;
+    }
     for (long long spin = 0; !read_check(ctx, seq, out); spin++) {
         if (spin % 1024 != 1023) continue;
         const hipError_t e = hipStreamQuery(ctx->stream);
@@ -846,7 +860,9 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         // most to be thrown away (a field fixed already, 4^4, check every 5, 16 and
         // 150 sweeps: 45, 45 and 45 us without, 68, 124 and 794 with; one period
         // of a run 108, 214 and 1561 without, 88, 195 and 1499 with).
-        const bool brief = !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
+        // Long periods wait as the process waits elsewhere, and so does everything where
+        // that is not by spinning.
+        const bool brief = waits_spin() && !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
         double before = 0.0;  // theta of the check before the last
         int taken = 0;
         const long long sweeps0 = ctx->sweeps_done;
@@ -866,7 +882,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
             }
             if (pending == 0) break;
             before = k.theta;
-            if ((rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
+            if ((rc = wait_check(ctx, ctx->checks + 1, &k, brief))) return rc;
             ctx->checks++;
             taken++;
             pending--;
@@ -1334,6 +1350,7 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
     log_open(ctx);
     ctx->log_calls++;
     *iters = 0;
+    const bool watch = waits_spin();  // the stream goes on behind the check
     if ((rc = start_checks(ctx))) return rc;
     int it = 0;
     for (;;) {
@@ -1355,7 +1372,7 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
             Check k{};
             if ((rc = sd_delta(ctx, U, true))) return rc;
             if (!first && (rc = sd_gfield(ctx, alpha))) return rc;
-            if ((rc = wait_check(ctx, ctx->checks + 1, &k))) return rc;
+            if ((rc = wait_check(ctx, ctx->checks + 1, &k, watch))) return rc;
             ctx->checks++;
             *F = k.F;
             *theta = k.theta;
