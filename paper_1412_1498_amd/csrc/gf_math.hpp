@@ -150,21 +150,26 @@ GF_HD double gf_atan2(double y, double x) {
 // phi = atan2(|b_vec|, b0) in [0, pi], n = -b_vec / |b_vec|:
 // g^omega = (cos(omega phi), n sin(omega phi)). A zero block gives g = 1;
 // g = -1 (b_vec = 0, b0 < 0) turns about the third axis.
+//
+// FULL (double links): |b_vec| and s / |b_vec| each by the product with the
+// reciprocal root and one correction. The products alone round once more than a
+// root and a quotient do (near the solution 6.5e-17 instead of 5.3e-17 rms at
+// omega 1.7); that is left so for float links, where the group element is rounded
+// to 6e-8 next.
+template <bool FULL = true>
 GF_HD void gf_su2_overrelax(const double b[4], double omega, double r[4]) {
     const TrigPtr T = gf_trig();
     const double v2 = fma(b[1], b[1], fma(b[2], b[2], b[3] * b[3]));
     const bool deg = !(v2 > 0.0);
     const double rv = deg ? 0.0 : gf_rsqrt(v2);  // 1 / |b_vec|
-    // |b_vec| and s / |b_vec| each by the product with rv and one correction: the
-    // products alone round once more than a root and a quotient do (near the
-    // solution 6.5e-17 instead of 5.3e-17 rms at omega 1.7)
     double vn = v2 * rv;
-    vn = fma(fma(-vn, vn, v2), 0.5 * rv, vn);
+    if (FULL) vn = fma(fma(-vn, vn, v2), 0.5 * rv, vn);
     const double phi = gf_atan2_upper(T, vn, b[0]);
     double s, c;
     gf_sincos(T, omega * phi, &s, &c);
     double f = s * rv;
-    f = -fma(fma(-vn, f, s), rv, f);
+    if (FULL) f = fma(fma(-vn, f, s), rv, f);
+    f = -f;
     r[0] = c;
     r[1] = b[1] * f;
     r[2] = b[2] * f;

@@ -25,9 +25,10 @@ namespace {
 
 struct Q4n { double v[4]; };
 
+template <typename R>
 __device__ __forceinline__ Q4n sun_su2_step(Q4n b, double omega) {
     Q4n r;
-    gf_su2_overrelax(b.v, omega, r.v);
+    gf_su2_overrelax<sizeof(R) == 8>(b.v, omega, r.v);
     return r;
 }
 
@@ -157,7 +158,7 @@ __device__ __forceinline__ void or_site_n(const CfgDesc &d, int p, int h, int su
             q.v[1] = 0.5 * (K.im[ab] + K.im[ba]);
             q.v[2] = 0.5 * (K.re[ab] - K.re[ba]);
             q.v[3] = 0.5 * (K.im[aa] - K.im[bb]);
-            const Q4n gq = sun_su2_step(q, d.omega);
+            const Q4n gq = sun_su2_step<R>(q, d.omega);
             rot_rows_n<N>(K, a, b, gq);
             rot_rows_n<N>(T, a, b, gq);
         }

@@ -70,11 +70,12 @@ __device__ __forceinline__ Cz cz_mul_conj(Cz a, Cz x) {
 
 // First row (al, be) of the SU(2) element g^omega of eq. (6) for the 2x2
 // block [[aa, ab], [ba, bb]] of K; the second row is (-conj be, conj al).
+template <typename R>
 __device__ __forceinline__ void subgroup_step(Cz aa, Cz ab, Cz ba, Cz bb, double omega, Cz &al, Cz &be) {
     const double q[4] = {0.5 * (aa.re + bb.re), 0.5 * (ab.im + ba.im), 0.5 * (ab.re - ba.re),
                          0.5 * (aa.im - bb.im)};
     double r[4];
-    gf_su2_overrelax(q, omega, r);
+    gf_su2_overrelax<sizeof(R) == 8>(q, omega, r);
     al = Cz{r[0], r[3]};
     be = Cz{r[2], r[1]};
 }
@@ -198,12 +199,12 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
     // row 0, K11 and K12 of row 1, then K21 and K22 of row 2.
     auto k_at = [&](int e) { return Cz{K.re[e], K.im[e]}; };
     Cz a1, b1, a2, b2, a3, b3;
-    subgroup_step(k_at(0), k_at(1), k_at(3), k_at(4), d.omega, a1, b1);
+    subgroup_step<R>(k_at(0), k_at(1), k_at(3), k_at(4), d.omega, a1, b1);
     const Cz k00 = rot_top(a1, b1, k_at(0), k_at(3)), k01 = rot_top(a1, b1, k_at(1), k_at(4)),
              k02 = rot_top(a1, b1, k_at(2), k_at(5));
     const Cz k11 = rot_bottom(a1, b1, k_at(1), k_at(4)), k12 = rot_bottom(a1, b1, k_at(2), k_at(5));
-    subgroup_step(k00, k02, k_at(6), k_at(8), d.omega, a2, b2);
-    subgroup_step(k11, k12, rot_bottom(a2, b2, k01, k_at(7)), rot_bottom(a2, b2, k02, k_at(8)), d.omega, a3, b3);
+    subgroup_step<R>(k00, k02, k_at(6), k_at(8), d.omega, a2, b2);
+    subgroup_step<R>(k11, k12, rot_bottom(a2, b2, k01, k_at(7)), rot_bottom(a2, b2, k02, k_at(8)), d.omega, a3, b3);
 
     // G = G3 G2 G1 (double), rounded to the link precision. With every G a 2x2
     // block and a 1, the rows are
