@@ -199,7 +199,9 @@ int sweep_lds(const Schedule &s, int nc, int nelem, double bytes) {
 // sweeps over every lane count, workgroup size, access kind and tile order on
 // lattices from 4^4 to 48^4 in all six forms of SU(3) links; the lines below
 // are within 2 % of the best schedule in the geometric mean.
-Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, double bytes, const gf_params &p) {
+// `most` and `hx`: bytes of the largest member and its half extent in x.
+Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, double bytes, double most, int hx,
+                          const gf_params &p) {
     Schedule s{};
     const bool f64 = prec == GF_F64, c8 = nc == 3 && nelem == 4;
     const double half = 0.5 * sites;
@@ -225,7 +227,7 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
         // in double 7.4 us with one lane, 5.5 us with four; 8-real 10.7 us with
         // one, 5.6 us with eight. From there two lanes, whose waves fit
         // two or three to a SIMD (double 20^4 32.9 -> 29.2 us), except float
-        // 12-real links beyond 1e5 sites, where one lane fits twice as well.
+        // 12-real links beyond 1.2e5 sites, where one lane fits twice as well.
         // Tiles in contiguous XCD shares: neighbouring tiles share the cache
         // lines at their seams (22x18x26x30 float 31.5 -> 29.0 us).
         if (c8) s.lps = half * 8 <= 512 * 64 ? 8 : half * 4 <= 1024 * 64 ? 4 : 2;
@@ -243,29 +245,57 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
         s.nt = 0;
         s.order = 0;
     } else {
-        // plain access keeps the end of one half-sweep in the last-level cache
-        // for the start of the next; of 3 GB in double (48^4) that is too little
-        // to pay (1121 us streaming, 1128 us plain). In float it pays up to some
-        // 4 GB: 48^3 x 96 (3.1 GB) 1112 us plain, one lane, 1165 us streaming in
-        // shares with two; 64^4 (4.8 GB) 1710 us streaming, two lanes in
-        // 256-thread workgroups, 1750 us in 128-thread ones. An ensemble is
-        // judged over its run, in which the small members retire early and the
-        // rest works on alone: 48^3 x 96 and 64 small lattices (5.4 GB), a sweep
-        // with all members active and with the large one alone: one lane, plain
-        // 4235 and 2355 us; two lanes, plain 4202 and 2474 (a run to 1e-7 5.91 s
-        // and 6.07 s); one lane, streaming 4373 and 2444. In double (7.8 GB) one
-        // lane, streaming 6746 and 4782, two lanes 6788 and 4827.
-        const bool large = bytes > (f64 ? 2.2e9 : 4e9), one = n == 1;
-        s.lps = f64 ? (large && !one ? 1 : 2) : large && one ? 2 : 1;
-        s.block = large && one && !f64 ? 256 : 128;
-        s.nt = large && (f64 || one);
-        s.order = large && f64 && one;
+        // Plain access keeps the end of one half-sweep in the last-level cache for
+        // the start of the next; the larger the field, the less that is of it, and
+        // streaming access moves the rest a little faster. It does so best where
+        // rows begin on whole 64-byte pieces (half extent in x a multiple of 8 in
+        // float), and not at all where the half extent is odd: runs of neighbouring
+        // rows then begin inside a 32-byte sector, which streaming likely fetches
+        // twice. A sweep with a check in ten, plain and streaming:
+        //   float   18-real 48^4 (1.5 GB) 1126 and 1137 us, 48^3 x 96 (3.1 GB) 2337 and
+        //           2278, 64^4 (4.8 GB) 3676 and 3474; on half pieces 56^4 (2.8 GB)
+        //           2147 and 2247, 56x64x56x64 (3.7 GB) 2855 and 2927, 72^4 (7.7 GB)
+        //           6513 and 6208; odd 66^4 (5.5 GB) 4590 and 4966
+        //           12-real 72^4 (5.2 GB) 3777 and 4182, 80^4 (7.9 GB) 5782 and 6103
+        //   double  18-real 48^4 (3.1 GB) 2371, two lanes streaming in shares 2324; odd
+        //           54^4 (4.9 GB) 4643 and 4179, one lane streaming 4097
+        //           12-real 60^4 (5.0 GB) 3702 and 4062, 64^4 (6.4 GB) 4788 and 4572
+        // An ensemble is judged over its run, in which the small members retire
+        // early and the largest works on alone: in float it takes that one's access
+        // (48^3 x 96 and 64 small lattices to 1e-7, 5.4 GB: one lane streaming 5.86 s,
+        // plain 5.93, two lanes plain 6.07); in double (7.8 GB, a sweep with all
+        // members active and with the largest alone) one lane streaming takes 6746 and
+        // 4782 us, two lanes 6788 and 4827.
+        const bool full = nelem == 9, even = hx % 2 == 0;
+        s.lps = f64 ? 2 : 1;
+        s.block = 128;
+        if (!f64) {
+            s.nt = full && (hx % 8 == 0 ? most > 2.2e9 : even && n == 1 && bytes > 5e9);
+        } else if (n > 1) {
+            if (bytes > 2.2e9) { s.lps = 1; s.nt = 1; }
+        } else if (full && bytes > 2.2e9) {
+            s.lps = even ? 2 : 1;
+            s.nt = 1;
+            s.order = even;
+        } else {
+            s.nt = !full && even && bytes > 5.5e9;
+        }
+        // What plain access leaves in the cache to be written back, a check behind
+        // every sweep pays for (48^4 in float: a check 375 us, 268 after a streaming
+        // sweep), and a sweep's gain is less than that from some 600 MB on where rows
+        // begin on whole sectors: with a check each, float 48^4 1458 us plain, 1404
+        // streaming, 12-real 968 and 926, double 32^4 548 and 521, 40^4 1454 and 1404;
+        // float 36^4 (0.5 GB) 459 and 473, 44^4 (half sectors) 1039 and 1056.
+        if (n == 1 && hx % (f64 ? 2 : 4) == 0 && bytes > 6e8 && p.lanes_per_site <= 0 && p.block_threads <= 0 && p.nontemporal < 0 &&
+            p.tile_order < 0)
+            s.nt_check = 1;
     }
     if (p.lanes_per_site > 0) s.lps = p.lanes_per_site;
     if (p.block_threads > 0) s.block = p.block_threads;
     if (p.nontemporal >= 0) s.nt = p.nontemporal;
     if (p.tile_order >= 0) s.order = p.tile_order;
     s.lds = sweep_lds(s, nc, nelem, bytes);
+    s.nt_check |= s.nt;
     return s;
 }
 
@@ -476,13 +506,16 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
     if (p.storage != GF_STORE_18 && p.storage != GF_STORE_12 && p.storage != GF_STORE_8) return GF_EINVAL;
     if (nc != 3 && p.storage != GF_STORE_18) return GF_EUNSUPPORTED;  // 12-/8-real are SU(3) only
     const int nelem = nc != 3 ? nc * nc : (p.storage == GF_STORE_12 ? 6 : p.storage == GF_STORE_8 ? 4 : 9);
-    double sites = 0.0, bytes = 0.0;
+    double sites = 0.0, bytes = 0.0, most = 0.0;
+    int hx = 0;
     for (int c = 0; c < n; c++) {
         const Geom g = make_geom(dims + 4 * c, nelem);
+        const double b = (double)field_complex(g) * (prec == GF_F64 ? 16 : 8);
         sites += g.V;
-        bytes += (double)field_complex(g) * (prec == GF_F64 ? 16 : 8);
+        bytes += b;
+        if (b > most) { most = b; hx = g.hx; }
     }
-    Schedule s = default_schedule(prec, nc, nelem, n, sites, bytes, p);
+    Schedule s = default_schedule(prec, nc, nelem, n, sites, bytes, most, hx, p);
     if (check_schedule(&tmp, s, nc) != GF_OK) return GF_EINVAL;
 
     gf_ctx *ctx = new gf_ctx();
@@ -811,10 +844,17 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
     };
     const bool graphs = ctx->p.use_graph && !ctx->p.timing && ctx->p.check_every <= 64;
     // one check period of m sweeps and its check, enqueued
+    auto sweeps = [&](int m, hipStream_t st) -> int {
+        const int nt = ctx->sched.nt;
+        if (m == 1) ctx->sched.nt = ctx->sched.nt_check;
+        const int r = full_sweeps(ctx, m, ctx->d_active, st);
+        ctx->sched.nt = nt;
+        return r;
+    };
     auto period = [&](int m) -> int {
         int r;
         if (!graphs) {
-            if ((r = full_sweeps(ctx, m, ctx->d_active, ctx->stream))) return r;
+            if ((r = sweeps(m, ctx->stream))) return r;
             return quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->stream);
         }
         unsigned long long pattern = 0;
@@ -829,7 +869,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
             hipGraphExec_t ge;
             const long long keep = ctx->sweeps_done;
             HIPTRY(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
-            int r1 = full_sweeps(ctx, m, ctx->d_active, ctx->cap_stream);
+            int r1 = sweeps(m, ctx->cap_stream);
             int r2 = r1 ? r1 : quality_launch(ctx, ctx->d_active, 1, m, eps, ctx->cap_stream);
             hipError_t ec = hipStreamEndCapture(ctx->cap_stream, &g);
             ctx->sweeps_done = keep;
@@ -992,6 +1032,7 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
             std::istringstream is(found);
             if (is >> s.lps >> s.block >> s.nt >> s.order && check_schedule(ctx, s, ctx->nc) == GF_OK) {
                 s.lds = sweep_lds(s, ctx->nc, ctx->nelem, total_bytes());
+                s.nt_check = s.nt;
                 ctx->sched = s;
                 return build_tiles(ctx);
             }
@@ -1063,7 +1104,7 @@ int gf_autotune(gf_ctx *ctx, void *const *U, double omega, const char *cache_pat
                 // others still carry the large members' tiles (measured on the uneven
                 // ensemble: tuned with every member active it won, then ran 11 % slower)
                 for (int order = 0; order < (ensemble ? 1 : 2) && rc == GF_OK; order++) {
-                    Schedule s{lps, block, nt, order, 0};
+                    Schedule s{lps, block, nt, order, 0, nt};
                     s.lds = sweep_lds(s, ctx->nc, ctx->nelem, total_bytes());
                     if (ctx->nc == 4 && s.lps < 2) continue;       // registers
                     float ms = measure(s, ctx->d_ones, ensemble ? 4 : 6);

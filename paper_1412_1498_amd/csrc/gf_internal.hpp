@@ -139,6 +139,7 @@ struct Schedule {
     int nt;         // non-temporal loads/stores
     int order;      // sweep tiles: 0 in dispatch order, 1 XCD-contiguous (xcd_tile)
     int lds;        // dynamic LDS per workgroup: unused by the kernel, it limits the workgroups on a CU
+    int nt_check;   // nt of a sweep between two checks (a fix driver's periods of one sweep)
 };
 
 // ---- launchers (defined in the .hip files) ----

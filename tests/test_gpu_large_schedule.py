@@ -1,0 +1,53 @@
+"""The default schedule of fields beyond the last-level cache, on both sides of its
+lines (contexts alone, no fields): full float links stream from 2.2 GB on where
+rows begin on 64-byte pieces, from 5 GB on where they begin on sectors, never with
+an odd half extent in x; full double ones from 2.2 GB on, with an odd half extent by
+one lane in dispatch order; 12-real links stay plain for longer. And runs with a check behind every sweep, which stream where the others do
+not, give the same links, checks and sweep counts as a plain schedule."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+F64, F32 = 0, 1
+RULE = [  # precision, storage form, dims, (lanes, workgroup, streaming, order)
+    (F32, 0, (48, 48, 48, 48), (1, 128, 0, 0)), (F32, 0, (56, 56, 56, 56), (1, 128, 0, 0)),
+    (F32, 0, (48, 48, 48, 96), (1, 128, 1, 0)), (F32, 0, (56, 64, 56, 64), (1, 128, 0, 0)),
+    (F32, 0, (64, 64, 64, 64), (1, 128, 1, 0)), (F32, 0, (68, 68, 68, 68), (1, 128, 1, 0)),
+    (F32, 0, (62, 62, 62, 62), (1, 128, 0, 0)), (F32, 0, (70, 70, 70, 70), (1, 128, 0, 0)),
+    (F32, 1, (64, 64, 64, 64), (1, 128, 0, 0)), (F32, 1, (72, 72, 72, 72), (1, 128, 0, 0)),
+    (F32, 1, (70, 70, 70, 70), (1, 128, 0, 0)),
+    (F64, 0, (40, 40, 40, 40), (2, 128, 0, 0)), (F64, 0, (42, 42, 42, 42), (2, 128, 0, 0)),
+    (F64, 0, (48, 48, 48, 48), (2, 128, 1, 1)), (F64, 0, (46, 46, 46, 46), (1, 128, 1, 0)),
+    (F64, 0, (54, 54, 54, 54), (1, 128, 1, 0)),
+    (F64, 1, (48, 48, 48, 48), (2, 128, 0, 0)), (F64, 1, (54, 54, 54, 54), (2, 128, 0, 0)),
+    (F64, 1, (64, 64, 64, 64), (2, 128, 1, 0)), (F64, 1, (66, 66, 66, 66), (2, 128, 0, 0)),
+]
+
+
+@pytest.mark.parametrize("prec,store,dims,want", RULE)
+def test_rule(prec, store, dims, want):
+    from paper_1412_1498_amd import gf
+    ctx = gf.Context(dims, prec=prec, params=gf.default_params(prec, storage=store))
+    assert tuple(ctx.schedule().values()) == want
+
+
+@pytest.mark.parametrize("prec,store,dims", [(F32, 0, (40, 40, 36, 38)), (F32, 1, (48, 40, 40, 46)),
+                                             (F64, 0, (32, 32, 32, 34)), (F64, 1, (36, 36, 36, 36)),
+                                             (F32, 0, (42, 40, 36, 38))])
+@pytest.mark.parametrize("graph", [0, 1])
+def test_a_check_behind_every_sweep(prec, store, dims, graph):
+    from paper_1412_1498_amd import gf, synth
+    kw = dict(storage=store, reunit_every=2)
+    a = gf.Context(dims, prec=prec, params=gf.default_params(prec, check_every=1, use_graph=graph, **kw))
+    b = gf.Context(dims, prec=prec, params=gf.default_params(prec, check_every=3, lanes_per_site=1, block_threads=64,
+                                                             nontemporal=0, tile_order=0, **kw))
+    assert a.field_bytes() > 6e8
+    U = a.pack(synth.random_gauge_field(dims, 0.4, 4, device="cuda").to(a.cdtype))
+    V = U.clone()
+    before = a.schedule()
+    r, q = a.fix(U, 1.7, 0.0, 3), b.fix(V, 1.7, 0.0, 3)
+    assert r == q and torch.equal(U, V) and a.schedule() == before
+    a.sweeps(U, 1.7, 2)
+    b.sweeps(V, 1.7, 2)
+    assert torch.equal(U, V)
