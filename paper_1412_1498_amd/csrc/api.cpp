@@ -562,7 +562,7 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
     }
     // in double a single lattice's F/theta walks time slices (its tiles' t neighbours
     // missed L2 in any slab order); in float the slab order is as fast
-    ctx->qstream = n == 1 && ctx->nc == 3 && prec == GF_F64 && quality_tstream_ok(ctx->desc[0].g);
+    ctx->qstream = n == 1 && ctx->nc == 3 && prec == GF_F64 && quality_tstream_ok(ctx->desc[0].g, nelem, ctx->desc[0].gauge);
     std::vector<int> qmap;
     for (int c = 0; c < n; c++) qmap.insert(qmap.end(), ctx->desc[c].nqtiles, c);
     if (hipMalloc(&ctx->d_desc, n * sizeof(CfgDesc)) != hipSuccess ||

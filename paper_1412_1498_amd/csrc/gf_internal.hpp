@@ -154,7 +154,7 @@ hipError_t launch_quality(int prec, int nelem, const CfgDesc *d_desc, const int 
 int quality_slice_chunks(const Geom &g);
 // k_quality for a single lattice whose time slices split into whole tiles,
 // walking runs of slices (same partials as launch_quality)
-bool quality_tstream_ok(const Geom &g);
+bool quality_tstream_ok(const Geom &g, int nelem, int gauge);
 hipError_t launch_quality_tstream(int prec, int nelem, const Geom &g, const CfgDesc *d_desc, const int *d_active,
                                   double *d_partials, hipStream_t st);
 hipError_t launch_quality_slices(int prec, int nelem, const CfgDesc &d, double *d_partials, double *d_out,

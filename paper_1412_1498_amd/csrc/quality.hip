@@ -395,11 +395,17 @@ hipError_t launch_quality(int prec, int nelem, const CfgDesc *d_desc, const int 
 
 // Whether k_quality_tstream takes lattice g (single lattices only): its slices
 // are whole tiles, and its runs are workgroups enough for the chip (eight a
-// CU). Whole calls in double, by slices and by tiles: 16^4 (48 runs) 39.7 and
-// 24.7 us, 32^4 (768 runs) 130 and 123 us, 48^4 (3456 runs) 555 and 576 us.
-bool quality_tstream_ok(const Geom &g) {
+// CU). Whole calls in double, by tiles and by slices: 16^4 (48 runs) 24.7 and 39.7
+// us, 32^4 (768 runs) 123 and 130, 48^4 (3456 runs) 576 and 555 us. Where rows
+// begin inside 128-byte lines (half extent in x no multiple of 8), so that a tile
+// shares the lines at its seams, the slices' fewer reads of 18-real and, in
+// Landau gauge, 12-real links count from 1400 runs on: 40^4 (1750 runs) 313 and
+// 281, 205 and 198; 40^3 x 36 284 and 248; 36x32x32x60 (1440) 255 and 248; but
+// 32x40x40x48 (1600) 267 and 274, and 8-real 40^4 192 and 210.
+bool quality_tstream_ok(const Geom &g, int nelem, int gauge) {
+    const bool early = g.hx % 8 != 0 && (nelem == 9 || (nelem == 6 && gauge == 0));
     return g.st % (QTILE / 2) == 0 && g.nt >= 2 &&
-           (long long)((g.nt + GF_QSTREAM_T - 1) / GF_QSTREAM_T) * (g.st / (QTILE / 2)) >= 2048;
+           (long long)((g.nt + GF_QSTREAM_T - 1) / GF_QSTREAM_T) * (g.st / (QTILE / 2)) >= (early ? 1400 : 2048);
 }
 
 template <typename R, int NE>
