@@ -494,10 +494,13 @@ hipError_t launch_gauge_transform(int prec, int nelem, const Geom &g, void *U, c
                                   hipStream_t st) {
     const dim3 grid((g.Vh + GT_TILE / 2 - 1) / (GT_TILE / 2));
     const SlabOrder so = make_slab_order(g.st, GT_TILE / 2, (int)grid.x, 64);
-    // Links that fit the last-level cache are better kept there (24^4 in float 59
-    // -> 52 us, 16^4 in double 25 -> 23 us a call); larger fields stream
-    // (48x44x40x36 in float 408 us, plain 449 us).
-    const bool nt = (double)field_complex(g) * (prec == 0 ? 16 : 8) > 150e6;
+    // Links that fit the last-level cache are better kept there (24^4 in float 71
+    // -> 65 us, 16^4 in double 38 -> 36 us a call); larger fields stream
+    // (48x44x40x36 in float 408 us, plain 449 us). In double the g field takes its
+    // share: 20^4 (92 + 23 MB) 71 us streaming, 68 plain, 24^4 with 8-real links
+    // (84 + 48 MB) 79 and 82, 26x22x30x34 (149 + 84 MB) 113 and 127.
+    const double bytes = (double)field_complex(g) * (prec == 0 ? 16 : 8);
+    const bool nt = prec == 0 ? bytes + (double)gfield_complex(g) * 16 > 120e6 : bytes > 150e6;
 #define GF_N(R, NE, NT)                                                                           \
     hipLaunchKernelGGL((k_gauge_transform<R, NE, NT>), grid, dim3(GT_TILE), 0, st, g, (V2<R>::type *)U, \
                        (const V2<R>::type *)gfield, so)
