@@ -343,6 +343,12 @@ void gf_host_trig(double x, double y, double out[3]);
  * Returns GF_EINVAL for NULL pointers or a bad precision. */
 int gf_host_link8(int prec, const double in[18], double stored[8], double out[18]);
 
+/* The schedule a context of n lattices (dims: 4 n extents) starts with: out =
+ * {lanes per site, workgroup size, streaming access, tile order, bytes of LDS
+ * set aside to limit the workgroups on a CU, streaming access of a sweep between
+ * two checks}. Returns GF_EINVAL for bad arguments. */
+int gf_host_schedule(int prec, int nc, int storage, int n, const int *dims, int out[6]);
+
 /* Index check: complex offsets of element 0 of the eight links (18-real
  * storage) that the site (parity, h) of a dims lattice updates in a
  * half-sweep: out[0..3] = U_mu(x), out[4..7] = U_mu(x - mu). Returns

@@ -286,9 +286,8 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
         // begin on whole sectors: with a check each, float 48^4 1458 us plain, 1404
         // streaming, 12-real 968 and 926, double 32^4 548 and 521, 40^4 1454 and 1404;
         // float 36^4 (0.5 GB) 459 and 473, 44^4 (half sectors) 1039 and 1056.
-        if (n == 1 && hx % (f64 ? 2 : 4) == 0 && bytes > 6e8 && p.lanes_per_site <= 0 && p.block_threads <= 0 && p.nontemporal < 0 &&
-            p.tile_order < 0)
-            s.nt_check = 1;
+        const bool asked = p.lanes_per_site > 0 || p.block_threads > 0 || p.nontemporal >= 0 || p.tile_order >= 0;
+        s.nt_check = n == 1 && hx % (f64 ? 2 : 4) == 0 && bytes > 6e8 && !asked;
     }
     if (p.lanes_per_site > 0) s.lps = p.lanes_per_site;
     if (p.block_threads > 0) s.block = p.block_threads;
@@ -297,6 +296,24 @@ Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, doub
     s.lds = sweep_lds(s, nc, nelem, bytes);
     s.nt_check |= s.nt;
     return s;
+}
+
+// The same for n lattices of the given extents.
+Schedule schedule_of(int prec, int nc, int nelem, int n, const int *dims, const gf_params &p) {
+    double sites = 0.0, bytes = 0.0, most = 0.0;
+    int hx = 0;
+    for (int c = 0; c < n; c++) {
+        const Geom g = make_geom(dims + 4 * c, nelem);
+        const double b = (double)field_complex(g) * (prec == GF_F64 ? 16 : 8);
+        sites += g.V;
+        bytes += b;
+        if (b > most) { most = b; hx = g.hx; }
+    }
+    return default_schedule(prec, nc, nelem, n, sites, bytes, most, hx, p);
+}
+
+int links_stored(int nc, int storage) {
+    return nc != 3 ? nc * nc : storage == GF_STORE_12 ? 6 : storage == GF_STORE_8 ? 4 : 9;
 }
 
 int check_schedule(gf_ctx *ctx, const Schedule &s, int nc) {
@@ -505,17 +522,8 @@ int create_impl(gf_ctx **out, int n, const int *dims, const int *gauge, int prec
     if (p.reunit_every < 0) return GF_EINVAL;
     if (p.storage != GF_STORE_18 && p.storage != GF_STORE_12 && p.storage != GF_STORE_8) return GF_EINVAL;
     if (nc != 3 && p.storage != GF_STORE_18) return GF_EUNSUPPORTED;  // 12-/8-real are SU(3) only
-    const int nelem = nc != 3 ? nc * nc : (p.storage == GF_STORE_12 ? 6 : p.storage == GF_STORE_8 ? 4 : 9);
-    double sites = 0.0, bytes = 0.0, most = 0.0;
-    int hx = 0;
-    for (int c = 0; c < n; c++) {
-        const Geom g = make_geom(dims + 4 * c, nelem);
-        const double b = (double)field_complex(g) * (prec == GF_F64 ? 16 : 8);
-        sites += g.V;
-        bytes += b;
-        if (b > most) { most = b; hx = g.hx; }
-    }
-    Schedule s = default_schedule(prec, nc, nelem, n, sites, bytes, most, hx, p);
+    const int nelem = links_stored(nc, p.storage);
+    const Schedule s = schedule_of(prec, nc, nelem, n, dims, p);
     if (check_schedule(&tmp, s, nc) != GF_OK) return GF_EINVAL;
 
     gf_ctx *ctx = new gf_ctx();
@@ -1438,6 +1446,21 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
 
 void gf_host_su2_step(const double b[4], double omega, double r[4]) {
     if (b && r) gf_su2_overrelax(b, omega, r);
+}
+
+int gf_host_schedule(int prec, int nc, int storage, int n, const int *dims, int out[6]) {
+    if (!dims || !out || n < 1 || (prec != GF_F64 && prec != GF_F32) || nc < 2 || nc > 4) return GF_EINVAL;
+    if (storage != GF_STORE_18 && (nc != 3 || (storage != GF_STORE_12 && storage != GF_STORE_8))) return GF_EINVAL;
+    gf_ctx tmp;
+    for (int c = 0; c < n; c++)
+        if (check_dims(&tmp, dims + 4 * c) != GF_OK) return GF_EINVAL;
+    gf_params p;
+    gf_params_default(&p, prec);
+    const Schedule s = schedule_of(prec, nc, links_stored(nc, storage), n, dims, p);
+    if (check_schedule(&tmp, s, nc) != GF_OK) return GF_EINVAL;
+    const int v[6] = {s.lps, s.block, s.nt, s.order, s.lds, s.nt_check};
+    std::copy(v, v + 6, out);
+    return GF_OK;
 }
 
 void gf_host_trig(double x, double y, double out[3]) {

@@ -93,6 +93,7 @@ def _load():
         "gf_host_su2_step": (None, [P, D, P]),
         "gf_host_trig": (None, [D, D, P]),
         "gf_host_link8": (I, [I, P, P, P]),
+        "gf_host_schedule": (I, [I, I, I, I, P, P]),
         "gf_site_links": (I, [P, I, LL, P]),
     }
     for name, (res, args) in sig.items():
@@ -433,6 +434,19 @@ def host_link8(prec, U):
         raise GFError(rc, "host_link8")
     o = np.array(out[:])
     return np.array(st[:]), (o[0::2] + 1j * o[1::2]).reshape(3, 3)
+
+
+def host_schedule(prec, dims, nc=3, storage=STORE_18):
+    """The schedule a context of these lattices (a list of dims, or one) starts
+    with: (lanes per site, workgroup size, streaming, tile order, LDS bytes that
+    limit the workgroups on a CU, streaming between two checks)."""
+    many = [dims] if isinstance(dims[0], int) else list(dims)
+    d = (ctypes.c_int * (4 * len(many)))(*[int(x) for m in many for x in m])
+    out = (ctypes.c_int * 6)()
+    rc = lib.gf_host_schedule(int(prec), int(nc), int(storage), len(many), d, out)
+    if rc != OK:
+        raise GFError(rc, "bad arguments")
+    return tuple(out)
 
 
 def site_links(dims, parity, h):

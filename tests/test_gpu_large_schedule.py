@@ -51,3 +51,22 @@ def test_a_check_behind_every_sweep(prec, store, dims, graph):
     a.sweeps(U, 1.7, 2)
     b.sweeps(V, 1.7, 2)
     assert torch.equal(U, V)
+
+
+@pytest.mark.parametrize("prec,nc,store,dims", [(F64, 3, 2, (32, 32, 32, 32)), (F32, 3, 2, (36, 40, 36, 38)),
+                                                (F32, 2, 0, (40, 36, 36, 38)), (F64, 4, 0, (24, 20, 26, 22)),
+                                                (F32, 4, 0, (24, 24, 28, 32))])
+def test_defaults_beyond_the_cache_give_the_same_bits(prec, nc, store, dims):
+    from paper_1412_1498_amd import gf, synth
+    a = gf.Context(dims, prec=prec, nc=nc, params=gf.default_params(prec, storage=store, reunit_every=2))
+    assert a.field_bytes() > 230e6
+    b = gf.Context(dims, prec=prec, nc=nc, params=gf.default_params(prec, storage=store, reunit_every=2,
+                                                                    lanes_per_site=4, block_threads=64,
+                                                                    nontemporal=1, tile_order=1))
+    A = synth.random_gauge_field(dims, 0.4, 6, device="cuda") if nc == 3 else \
+        synth.random_sun_field(dims, nc, 0.4, 6).to("cuda")
+    U = a.pack(A.to(a.cdtype))
+    V = U.clone()
+    a.sweeps(U, 1.7, 3)
+    b.sweeps(V, 1.7, 3)
+    assert torch.equal(U, V)
