@@ -8,12 +8,13 @@
 // sincos: argument in [0, 2 pi]. Quadrant reduction x = k pi/2 + r (k =
 //   rint(2x/pi), r in [-pi/4, pi/4]) with pi/2 split into a double head and
 //   a tail (Cody and Waite's method), each subtracted with one fused
-//   multiply-add; then minimax polynomials of sin r (to r^13, error 2^-58)
-//   and cos r (to r^14, 2^-64).
+//   multiply-add; then minimax polynomials of sin r (to r^13, error 2^-57.6)
+//   and cos r (to r^14, 2^-59.9).
 // atan2: the vector (|x|, |y|) is turned by the nearest of 0, pi/4, pi/2, so
 //   that the one quotient left is u in [-tan(pi/8), tan(pi/8)]; there atan u
-//   is a minimax polynomial to u^23 (relative error 2^-59).
-// The polynomials (Remez exchange in 50 digits, rounded to double) are
+//   is a minimax polynomial to u^23 (relative error 2^-58.5).
+// The polynomials (Remez exchange in 50 digits, coefficients rounded to double;
+// the errors are those with the rounded coefficients, exactly evaluated) are
 // evaluated by Estrin's scheme: their pairs are independent, so the chain is
 // a third of Horner's.
 #pragma once

@@ -1,7 +1,6 @@
-// su3_device.hpp -- register-level SU(3)/SU(2) arithmetic for the gfx950
-// kernels of libgf: link loads/stores in the even/odd element-major layout,
-// the SU(2) subgroup solve with exact over-relaxation, row rotations, and
-// Gram-Schmidt reunitarisation.
+// su3_device.hpp -- what the gfx950 kernels of libgf share: sums across the
+// lanes of a site and of a wave in registers, link loads and stores in the
+// even/odd element-major layout, and Gram-Schmidt reunitarisation.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -179,53 +178,6 @@ __device__ __forceinline__ void store_link(const Mat<R> &m, gchar *base, long lo
     }
 }
 
-// m <- m^dagger when `flip` (a per-lane flag), else unchanged.
-template <typename R>
-__device__ __forceinline__ void dagger_if(Mat<R> &m, bool flip) {
-#pragma unroll
-    for (int r = 0; r < 3; r++) {
-#pragma unroll
-        for (int c = r; c < 3; c++) {
-            const int a = 3 * r + c, b = 3 * c + r;
-            R ar = m.re[a], ai = m.im[a], br = m.re[b], bi = m.im[b];
-            m.re[a] = flip ? br : ar;
-            m.im[a] = flip ? -bi : ai;
-            m.re[b] = flip ? ar : br;
-            m.im[b] = flip ? -ai : bi;
-        }
-    }
-}
-
-// Quaternion part of the (a, b) block of m, times 2:
-//   t0 = Re(m_aa + m_bb), t1 = Im(m_ab + m_ba), t2 = Re(m_ab - m_ba), t3 = Im(m_aa - m_bb)
-template <typename R>
-__device__ __forceinline__ void block_quat2(const Mat<R> &m, int a, int b, double t[4]) {
-    const int aa = 4 * a, bb = 4 * b, ab = 3 * a + b, ba = 3 * b + a;
-    t[0] = (double)m.re[aa] + (double)m.re[bb];
-    t[1] = (double)m.im[ab] + (double)m.im[ba];
-    t[2] = (double)m.re[ab] - (double)m.re[ba];
-    t[3] = (double)m.im[aa] - (double)m.im[bb];
-}
-
-// Rows a, b of m <- G (rows a, b of m), G = [[g0 + i g3, g2 + i g1],
-// [-g2 + i g1, g0 - i g3]] given in the link precision.
-template <typename R>
-__device__ __forceinline__ void rotate_rows(Mat<R> &m, int a, int b, const R g[4]) {
-    const R ar = g[0], ai = g[3];   // alpha
-    const R br = g[2], bi = g[1];   // beta
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        const R xr = m.re[3 * a + c], xi = m.im[3 * a + c];
-        const R yr = m.re[3 * b + c], yi = m.im[3 * b + c];
-        // row a: alpha x + beta y
-        m.re[3 * a + c] = fma(ar, xr, fma(-ai, xi, fma(br, yr, -bi * yi)));
-        m.im[3 * a + c] = fma(ar, xi, fma(ai, xr, fma(br, yi, bi * yr)));
-        // row b: -conj(beta) x + conj(alpha) y
-        m.re[3 * b + c] = fma(-br, xr, fma(-bi, xi, fma(ar, yr, ai * yi)));
-        m.im[3 * b + c] = fma(-br, xi, fma(bi, xr, fma(ar, yi, -ai * yr)));
-    }
-}
-
 // r / |r| for a row of three complex numbers. Rows of float links take one
 // reciprocal square root and six products (the result is rounded to float);
 // double links keep the correctly rounded quotients.
@@ -276,13 +228,6 @@ __device__ __forceinline__ void reunitarise(Mat<R> &m) {
         m.re[c] = (R)r0r[c]; m.im[c] = (R)r0i[c];
         m.re[3 + c] = (R)r1r[c]; m.im[3 + c] = (R)r1i[c];
     }
-}
-
-// Binary-tree sum s[0..N) as ((s0 + s1) + (s2 + s3)) + ...
-template <int N>
-__device__ __forceinline__ double tree_sum(const double *s) {
-    if constexpr (N == 1) return s[0];
-    else return tree_sum<N / 2>(s) + tree_sum<N / 2>(s + N / 2);
 }
 
 __device__ __forceinline__ int pick4(const int v[4], int i) {

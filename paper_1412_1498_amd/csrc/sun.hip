@@ -235,7 +235,9 @@ hipError_t launch_sun_lps(const Schedule &s, const CfgDesc *d_desc, const int *d
     }
 }
 
-// Canonical AoS [site][mu][N][N] <-> blocked layout; one thread per link.
+// Canonical AoS [site][mu][N][N] <-> blocked layout: the tiles of the SU(3) packer,
+// a lane per link between LDS and the blocked layout. Packing zeroes the rest of
+// a parity's last block.
 template <typename R, int N, bool UNPACK>
 __global__ void __launch_bounds__(PACK_BLOCK) k_sun_pack(Geom g, typename V2<R>::type *__restrict__ aos,
                                                          typename V2<R>::type *__restrict__ U) {
