@@ -197,8 +197,9 @@ int sweep_lds(const Schedule &s, int nc, int nelem, double bytes) {
 
 // Default schedule by lattice size (`sites` and `bytes` of all members), from
 // sweeps over every lane count, workgroup size, access kind and tile order on
-// lattices from 4^4 to 48^4 in all six forms of SU(3) links; the lines below
-// are within 2 % of the best schedule in the geometric mean.
+// lattices from 4^4 to 48^4 in all six forms of SU(3) links (the lines are within
+// 2 % of the best schedule there in the geometric mean) and over access kinds
+// and orders up to 80^4.
 // `most` and `hx`: bytes of the largest member and its half extent in x.
 Schedule default_schedule(int prec, int nc, int nelem, int n, double sites, double bytes, double most, int hx,
                           const gf_params &p) {

@@ -9,8 +9,8 @@
 // line of a wavefront's 4.6 or 9.2 KB once per element instead. So a
 // workgroup copies the canonical run with 16-byte accesses and takes the
 // links from LDS (the other way round to unpack). Links at 48^4, float
-// 18-real: pack 628 -> 569 us, unpack 883 -> 549 us (5.5
-// TB/s); double 1145 -> 1124 and 1564 -> 1127 us; SU(4) float at 24^4 172 -> 52
+// 18-real: pack 628-647 -> 541-569 us, unpack 883-894 -> 549-585 us (5.2 to 5.6
+// TB/s); double 1145 -> 1118 and 1564 -> 1127-1157 us; SU(4) float at 24^4 172 -> 52
 // and 415 -> 49 us; algebra fields in double 239 -> 115 and 397 -> 110 us.
 #pragma once
 

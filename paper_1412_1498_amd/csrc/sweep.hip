@@ -22,10 +22,10 @@
 // neighbours), hence the lane count, workgroup size and occupancy limit by
 // lattice size in default_schedule (api.cpp). Half-sweeps at 48^4, before and
 // after the solve was shortened, its registers trimmed and the tiles taken
-// from alternating ends: float 18-real 546-552 -> 530-534 us, 12-real 373 ->
-// 334, 8-real 372 -> 260, double 18-real 1146 -> 1121, 8-real 684 -> 487;
-// at 22x18x26x30 42.2 -> 29.3, 27.0 -> 21.8, 31.6 -> 21.4, 79.1 -> 53.7,
-// 52.8 -> 30.6.
+// from alternating ends: float 18-real 546-552 -> 535 us, 12-real 373 -> 342,
+// 8-real 372 -> 259, double 18-real 1146 -> 1123-1136, 8-real 684 -> 492-500;
+// at 22x18x26x30 42.2 -> 30.7, 27.0 -> 22.4, 31.6 -> 21.5, 79.1 -> 54.1,
+// 52.8 -> 32.2.
 //
 // Schedules: LPS lanes cooperate on a site (LPS = 1, 2, 4, 8), each holding
 // 8/LPS links. Link slots are ordered (fwd 0, bwd 0, fwd 1, bwd 1, ...,
@@ -163,7 +163,7 @@ __device__ __forceinline__ void or_site(const CfgDesc &d, int p, int h, int sub)
     // then waits for several memory latencies instead of one. Not for full float
     // links streamed by one lane, the access of fields far beyond the last-level
     // cache: there the memory is busy anyway, and fewer loads at a time disturb
-    // each other less (48^3 x 96 2382 -> 2217 us a sweep, 48^4 1164 -> 1106)
+    // each other less (48^3 x 96 2360 -> 2211 us a sweep, 48^4 1164 -> 1106)
     if constexpr (!(NT && LPS == 1 && NE == 9 && sizeof(R) == 4)) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < L; k++) unpack_link<R, NE>(raw[k], w[k]);
