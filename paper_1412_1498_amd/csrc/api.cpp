@@ -478,8 +478,11 @@ int start_checks(gf_ctx *ctx) {
 // well) or has asked for waits that leave the core to others.
 bool waits_spin() {
     unsigned flags = 0;
-    return hipGetDeviceFlags(&flags) != hipSuccess ||
-           !(flags & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync));
+    if (hipGetDeviceFlags(&flags) != hipSuccess) {
+        (void)hipGetLastError();  // not the next launch's error
+        return true;
+    }
+    return !(flags & (hipDeviceScheduleYield | hipDeviceScheduleBlockingSync));
 }
 
 // Wait for check number `seq`: by the runtime's own wait for the stream, or (watch)
@@ -852,7 +855,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         for (int c = 0; c < n; c++) was_active[c] = ctx->h_flags[c];
     };
     const bool graphs = ctx->p.use_graph && !ctx->p.timing && ctx->p.check_every <= 64;
-    // one check period of m sweeps and its check, enqueued
+    // the sweeps of a period: one alone with the access of a sweep between two checks
     auto sweeps = [&](int m, hipStream_t st) -> int {
         const int nt = ctx->sched.nt;
         if (m == 1) ctx->sched.nt = ctx->sched.nt_check;
@@ -860,6 +863,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         ctx->sched.nt = nt;
         return r;
     };
+    // one check period of m sweeps and its check, enqueued
     auto period = [&](int m) -> int {
         int r;
         if (!graphs) {
@@ -909,9 +913,11 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
         // most to be thrown away (a field fixed already, 4^4, check every 5, 16 and
         // 150 sweeps: 45, 45 and 45 us without, 68, 124 and 794 with; one period
         // of a run 108, 214 and 1561 without, 88, 195 and 1499 with).
-        // Long periods wait as the process waits elsewhere, and so does everything where
-        // that is not by spinning.
-        const bool brief = waits_spin() && !ctx->p.timing && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
+        // The record is watched where the process's waits spin anyway; it is there some
+        // 5 us before the runtime's own wait ends (32^4 12-real, a check every ten sweeps:
+        // 2626 us for twenty, 2613 watched).
+        const bool watch = waits_spin() && !ctx->p.timing;
+        const bool brief = watch && (double)ctx->desc[0].g.V * ctx->p.check_every <= 4e6;
         double before = 0.0;  // theta of the check before the last
         int taken = 0;
         const long long sweeps0 = ctx->sweeps_done;
@@ -931,7 +937,7 @@ int gf_batch_fix(gf_ctx *ctx, void *const *U, const double *omega, double eps, i
             }
             if (pending == 0) break;
             before = k.theta;
-            if ((rc = wait_check(ctx, ctx->checks + 1, &k, brief))) return rc;
+            if ((rc = wait_check(ctx, ctx->checks + 1, &k, watch))) return rc;
             ctx->checks++;
             taken++;
             pending--;
@@ -1400,7 +1406,7 @@ int gf_sd_fix(gf_ctx *ctx, void *U, double alpha, double eps, int max_iter, int 
     log_open(ctx);
     ctx->log_calls++;
     *iters = 0;
-    const bool watch = waits_spin();  // the stream goes on behind the check
+    const bool watch = waits_spin() && !ctx->p.timing;  // the stream goes on behind the check
     if ((rc = start_checks(ctx))) return rc;
     int it = 0;
     for (;;) {
